@@ -120,28 +120,30 @@ __device__ __forceinline__ void st_stream2(void* p, uint2 v) {
 #define HQ_NT_P_ST 0
 #endif
 
+// The 16 / bytes elements of one 16-byte piece, widened to fp32.
+template <int DT>
+__device__ __forceinline__ void widen_piece(const uint4& a, float* v) {
+  const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if constexpr (DT == kF32) {
+      v[j] = __uint_as_float(w[j]);
+    } else if constexpr (DT == kF16) {
+      v[2 * j] = h2f(w[j] & 0xFFFFu);
+      v[2 * j + 1] = h2f(w[j] >> 16);
+    } else {
+      v[2 * j] = bf2f(w[j] & 0xFFFFu);
+      v[2 * j + 1] = bf2f(w[j] >> 16);
+    }
+  }
+}
+
 // Load 8 consecutive elements starting at p (16-byte aligned for fp16/bf16,
 // 32-byte aligned for fp32; streaming) and widen them to fp32.
 template <int DT, bool NT = true>
 __device__ __forceinline__ void load8(const void* p, float v[8]) {
-  if constexpr (DT == kF32) {
-    const uint4 a = ld_stream<NT>(p), b = ld_stream<NT>(static_cast<const char*>(p) + 16);
-    v[0] = __uint_as_float(a.x); v[1] = __uint_as_float(a.y); v[2] = __uint_as_float(a.z); v[3] = __uint_as_float(a.w);
-    v[4] = __uint_as_float(b.x); v[5] = __uint_as_float(b.y); v[6] = __uint_as_float(b.z); v[7] = __uint_as_float(b.w);
-  } else {
-    uint4 a = ld_stream<NT>(p);
-    uint32_t w[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if constexpr (DT == kF16) {
-        v[2 * j] = h2f(w[j] & 0xFFFFu);
-        v[2 * j + 1] = h2f(w[j] >> 16);
-      } else {
-        v[2 * j] = bf2f(w[j] & 0xFFFFu);
-        v[2 * j + 1] = bf2f(w[j] >> 16);
-      }
-    }
-  }
+  widen_piece<DT>(ld_stream<NT>(p), v);
+  if constexpr (DT == kF32) widen_piece<DT>(ld_stream<NT>(static_cast<const char*>(p) + 16), v + 4);
 }
 
 // Store n (multiple of 4) fp32 values, converting to the element type.

@@ -57,6 +57,22 @@ __device__ __forceinline__ void load16(const char* p, float v[16]) {
   load8<DT, NT>(p + 8 * Elem<DT>::bytes, v + 8);
 }
 
+// The same in two parts, so that a load can be issued well before its values are widened (a
+// widening in the load's own basic block would wait for it there).
+template <int DT>
+struct Raw16 {
+  uint4 q[Elem<DT>::bytes];
+  template <bool NT>
+  __device__ __forceinline__ void load(const char* p) {
+#pragma unroll
+    for (int i = 0; i < Elem<DT>::bytes; ++i) q[i] = ld_stream<NT>(p + 16 * i);
+  }
+  __device__ __forceinline__ void widen(float v[16]) const {
+#pragma unroll
+    for (int i = 0; i < Elem<DT>::bytes; ++i) widen_piece<DT>(q[i], v + i * (16 / Elem<DT>::bytes));
+  }
+};
+
 // Value of lane (lane ^ M), M in {1, 2, 4}, added to x: DPP quad permutations (folded into
 // the add) or a ds_swizzle swap of 4-lane groups.
 template <int M>
@@ -156,30 +172,63 @@ __device__ __forceinline__ int sumsq8(uint32_t w, int acc) {
   return __builtin_amdgcn_sdot8((int)w, (int)w, acc, false);
 }
 
-// Sum over the G lanes of a row group (G a power of two; every lane of the group active).
-__device__ __forceinline__ int group_sum(int v, int G) {
-  for (int o = G >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o);
+// Sum over the 2^log2g threads of a row group, for every thread of it.  Groups inside a wave
+// add by DPP (swap neighbours, swap pairs, mirror halves, mirror the row of 16), one lane
+// exchange for 32 and the four row sums as scalars for 64; wider groups add their waves'
+// sums through LDS, `red` holding two buffers of kQWaves words used in turn (a buffer is
+// written again only after the barrier of the call in between).  Every thread of the
+// workgroup calls it where log2g > 6, every lane of the wave otherwise.
+__device__ __forceinline__ int group_sum(int v, int log2g, int* red, int& par) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);  // log2g >= 2 always
+  v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);
+  if (log2g == 2) return v;
+  v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);
+  if (log2g == 3) return v;
+  v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true);
+  if (log2g == 4) return v;
+  if (log2g == 5) return v + __shfl_xor(v, 16);
+  v = __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
+      __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
+  if (log2g == 6) return v;
+  const int w = threadIdx.x >> 6, n = 1 << (log2g - 6);
+  if ((threadIdx.x & 63) == 0) red[par * kQWaves + w] = v;
+  __syncthreads();
+  v = 0;
+  for (int i = 0; i < n; ++i) v += red[par * kQWaves + (w & ~(n - 1)) + i];
+  par ^= 1;
   return v;
 }
 
+// Lanes without a chunk of their own load chunk (lane & mask) of a row instead.  They must
+// form whole Hadamard blocks, or their transform could exceed the tensor's maximum: blocks
+// of 128 columns (8 lanes) need rows of whole 8 chunks, shorter blocks fit 4.
+__device__ __forceinline__ int spare_mask(int row_chunks) { return row_chunks % 8 == 0 ? 7 : 3; }
+
 // Row-group geometry of one job (one tensor).  The wave walks a uniform sequence of steps
 // (row k of its groups, 16-column chunk it), kept several steps ahead in loads whatever
-// the row boundaries; group rows past the end re-read the last row and store nothing.
+// the row boundaries; group rows past the end re-read the last row and store nothing, and
+// so do the lanes past a row's last chunk where G does not divide the row (they load one of
+// its first chunks).  Groups wider than a wave (log2g > 6) take the same number of steps in
+// every wave of the workgroup.
 struct Geo {
-  int lane, sub, grp, G, rpw, iters;
+  int lane, sub, G, iters, chunks, spare;
+  bool ragged;
   int64_t first_row, row_step, rows, steps;
   __device__ Geo(const QJob& j, int wg) {
     lane = threadIdx.x & 63;
     G = 1 << j.log2g;
-    sub = lane & (G - 1);
-    grp = lane >> j.log2g;
-    rpw = 64 >> j.log2g;
-    iters = (int)((j.cols / kVE) >> j.log2g);
-    const int64_t wave_row0 = ((int64_t)wg * kQWaves + (threadIdx.x >> 6)) * rpw;
-    first_row = wave_row0 + grp;
-    row_step = (int64_t)j.wg * kQWaves * rpw;
+    sub = threadIdx.x & (G - 1);
+    chunks = (int)(j.cols / kVE);
+    iters = (chunks + G - 1) >> j.log2g;
+    ragged = iters * G != chunks;
+    spare = spare_mask(chunks);
+    const int rw = kQThreads >> j.log2g;  // rows of a workgroup at a time
+    const int64_t wg_row0 = (int64_t)wg * rw;
+    first_row = wg_row0 + (threadIdx.x >> j.log2g);
+    row_step = (int64_t)j.wg * rw;
     rows = j.rows;
-    steps = wave_row0 < rows ? (rows - wave_row0 + row_step - 1) / row_step * iters : 0;
+    const int64_t row0 = j.log2g <= 6 ? wg_row0 + ((threadIdx.x & ~63u) >> j.log2g) : wg_row0;
+    steps = row0 < rows ? (rows - row0 + row_step - 1) / row_step * iters : 0;
   }
   // row of step (k, it) for this lane's group, clamped into the tensor
   __device__ int64_t row_of(int64_t k) const {
@@ -187,13 +236,46 @@ struct Geo {
     return r < rows ? r : rows - 1;
   }
   __device__ bool valid(int64_t k) const { return first_row + k * row_step < rows; }
+  // 16-column chunk of step (k, it), whether the row has it, and the first of its columns, or
+  // where it has not, that of the chunk this lane loads instead (the ragged test is uniform)
+  __device__ int chunk(int it) const { return it * G + sub; }
+  __device__ bool live(int it) const { return !ragged || chunk(it) < chunks; }
+  __device__ int load_col(int it) const {
+    int c = it * (G * kVE) + sub * kVE;
+    if (ragged && chunk(it) >= chunks) c = (sub & spare) * kVE;
+    return c;
+  }
+};
+
+// Geometry of the block-size search, which has no per-row results: the tensor is one run of
+// 16-element chunks, 64 to a wave and step, whatever its rows: a row is a multiple of 64
+// elements and of the Hadamard block, so blocks never straddle a row and stay aligned.
+// Lanes past the end load one of the first chunks, a whole block of lanes at a time.
+struct Flat {
+  int lane, spare;
+  int64_t wave, waves, chunks, steps;
+  __device__ Flat(const QJob& j, int wg) {
+    lane = threadIdx.x & 63;
+    wave = (int64_t)wg * kQWaves + (threadIdx.x >> 6);
+    waves = (int64_t)j.wg * kQWaves;
+    chunks = j.rows * (j.cols / kVE);
+    spare = spare_mask((int)(j.cols / kVE));
+    const int64_t all = (chunks + 63) / 64;
+    steps = wave < all ? (all - wave + waves - 1) / waves : 0;
+  }
+  __device__ int64_t chunk(int64_t s) const { return (wave + s * waves) * 64 + lane; }
+  __device__ bool valid(int64_t s) const { return chunk(s) < chunks; }
+  __device__ int64_t load_chunk(int64_t s) const { return valid(s) ? chunk(s) : (lane & spare); }
 };
 
 // max over the first n partial maxima (every thread of the workgroup gets it).
 __device__ __forceinline__ float reduce_parts(const float* __restrict__ part, int n) {
   __shared__ float red[kQWaves];
   float m = 0.f;
-  for (int i = threadIdx.x; i < n; i += kQThreads) m = fmaxf(m, part[i]);
+  for (int i = threadIdx.x; i < n; i += 2 * kQThreads) {  // both loads in flight at once
+    const float p0 = part[i], p1 = part[i + kQThreads < n ? i + kQThreads : i];
+    m = fmaxf(m, fmaxf(p0, p1));
+  }
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
@@ -242,7 +324,7 @@ __global__ __launch_bounds__(kQThreads) void fwht_absmax_kernel(QJob j0, QJob j1
   const Geo g(j, wg);
   constexpr int EB = Elem<DT>::bytes;
   float m = 0.f;
-  const char* base = static_cast<const char*>(j.src) + ((int64_t)q.b * j.bstride + (int64_t)g.sub * kVE) * EB;
+  const char* base = static_cast<const char*>(j.src) + (int64_t)q.b * j.bstride * EB;
   int64_t k = 0;
   int it = 0;
   for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
@@ -250,13 +332,13 @@ __global__ __launch_bounds__(kQThreads) void fwht_absmax_kernel(QJob j0, QJob j1
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
-        load16<DT, HQ_NT_ABS_LD>(base + (g.row_of(k) * j.cols + (int64_t)it * g.G * kVE) * EB, v[u]);
+        load16<DT, HQ_NT_ABS_LD>(base + (g.row_of(k) * j.cols + g.load_col(it)) * EB, v[u]);
         if (++it == g.iters) { it = 0; ++k; }
       }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (s0 + u < g.steps) {  // duplicated rows leave the maximum unchanged
+      if (s0 + u < g.steps) {  // rows and chunks loaded twice leave the maximum unchanged
         fwht16<LOG2B>(v[u], g.lane);
 #pragma unroll
         for (int e = 0; e < kVE; e += 2) m = fmaxf(m, fmaxf(fabsf(v[u][e]), fabsf(v[u][e + 1])));
@@ -290,8 +372,9 @@ template <int LOG2B> struct TileT {
 
 // LSQ selects the learned-step quantiser: code clamp(rint(v inv), -7, 7) (the clamp first)
 // and delta as in fwht_lsq_kernel; else the code rint(v inv) of fwht_quant_kernel.
-template <int DT, int LOG2B, bool LSQ>
-__device__ void quant_tile(const void* src, int64_t rows, int64_t cols, float inv, int t,
+// inv_of() gives the scale; it is called after the tile's loads were issued.
+template <int DT, int LOG2B, bool LSQ, class F>
+__device__ void quant_tile(const void* src, int64_t rows, int64_t cols, F&& inv_of, int t,
                            uint8_t* __restrict__ packed, uint16_t* __restrict__ delta,
                            uint8_t* __restrict__ packed_t, uint8_t* __restrict__ fp6 = nullptr) {
   using T = TileT<LOG2B>;
@@ -306,6 +389,7 @@ __device__ void quant_tile(const void* src, int64_t rows, int64_t cols, float in
     const int64_t r = ok ? r0 + rr : rows - 1;
     float v[kVE];
     load16<DT, HQ_NT_Q_LD>(static_cast<const char*>(src) + (r * cols + c0 + sub * kVE) * EB, v);
+    const float inv = inv_of();
     fwht16<LOG2B>(v, tid & 63);
     uint32_t y[kVE], dh[kVE / 2];
 #pragma unroll
@@ -366,56 +450,68 @@ template <int DT, int LOG2B>
 __global__ __launch_bounds__(kQThreads) void fwht_quant_kernel(QJob j0, QJob j1, QOut o0, QOut o1) {
   constexpr int U = 2;  // steps in flight (2 measured faster than 4, as for the maximum)
   if ((int)blockIdx.x >= j0.wg + j1.wg) {  // uniform per workgroup
-    const float a = reduce_parts(o1.part, o1.nparts);
     const int t = (int)blockIdx.x - j0.wg - j1.wg;
-    if (t == 0 && threadIdx.x == 0) *o1.amax_out = a;
-    quant_tile<DT, LOG2B, false>(j1.src, j1.rows, j1.cols, a > 0.f ? 7.0f / a : 0.f, t, o1.packed,
-                                 nullptr, o1.packed_t, o1.fp6);
+    auto inv_of = [&]() {
+      const float a = reduce_parts(o1.part, o1.nparts);
+      if (t == 0 && threadIdx.x == 0) *o1.amax_out = a;
+      return a > 0.f ? 7.0f / a : 0.f;
+    };
+    quant_tile<DT, LOG2B, false>(j1.src, j1.rows, j1.cols, inv_of, t, o1.packed, nullptr,
+                                 o1.packed_t, o1.fp6);
     return;
   }
   const bool second = (int)blockIdx.x >= j0.wg;
   const QJob& j = second ? j1 : j0;
   const QOut& o = second ? o1 : o0;
   const int wg = second ? (int)blockIdx.x - j0.wg : (int)blockIdx.x;
-  const float a = reduce_parts(o.part, o.nparts);
-  if (wg == 0 && threadIdx.x == 0) *o.amax_out = a;
-  const float inv = a > 0.f ? 7.0f / a : 0.f;
   const Geo g(j, wg);
   constexpr int EB = Elem<DT>::bytes;
-  const char* base = static_cast<const char*>(j.src) + (int64_t)g.sub * kVE * EB;
+  const char* base = static_cast<const char*>(j.src);
+  __shared__ int rsum[2 * kQWaves];
+  int par = 0;
   int64_t k = 0, kp = 0;  // load and process positions
   int it = 0, ip = 0;
   int ss = 0;
-  for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
-    float v[U][kVE];
+  Raw16<DT> raw[U];
+  auto load = [&](int64_t s0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
-        load16<DT, HQ_NT_Q_LD>(base + (g.row_of(k) * j.cols + (int64_t)it * g.G * kVE) * EB, v[u]);
+        raw[u].template load<HQ_NT_Q_LD>(base + (g.row_of(k) * j.cols + g.load_col(it)) * EB);
         if (++it == g.iters) { it = 0; ++k; }
       }
     }
+  };
+  load(0);  // in flight while the maximum is formed
+  const float a = reduce_parts(o.part, o.nparts);
+  if (wg == 0 && threadIdx.x == 0) *o.amax_out = a;
+  const float inv = a > 0.f ? 7.0f / a : 0.f;
+  for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
+    if (s0) load(s0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
-        fwht16<LOG2B>(v[u], g.lane);
+        float v[kVE];
+        raw[u].widen(v);
+        fwht16<LOG2B>(v, g.lane);
         uint32_t y[kVE];
 #pragma unroll
-        for (int e = 0; e < kVE; ++e) y[e] = rne_bits(v[u][e] * inv);
+        for (int e = 0; e < kVE; ++e) y[e] = rne_bits(v[e] * inv);
         const uint32_t w0 = pack8_bits(y), w1 = pack8_bits(y + 8);
-        ss = sumsq8(w1, sumsq8(w0, ss));
-        const bool ok = g.valid(kp);
+        const int c = g.chunk(ip);
+        const bool live = g.live(ip);
+        ss = live ? sumsq8(w1, sumsq8(w0, ss)) : ss;
+        const bool in_row = g.valid(kp), ok = live && in_row;
         const int64_t r = g.row_of(kp);
-        if (ok) st_stream2<HQ_NT_Q_ST>(reinterpret_cast<uint2*>(o.packed + r * (j.cols / 2)) + (int64_t)ip * g.G + g.sub, make_uint2(w0, w1));
+        if (ok) st_stream2<HQ_NT_Q_ST>(reinterpret_cast<uint2*>(o.packed + r * (j.cols / 2)) + c, make_uint2(w0, w1));
         if (o.fp6) {  // the pair exchange runs in every lane, the store only in valid rows
-          const int64_t c = (int64_t)ip * g.G + g.sub;
           const uint4 f6 = fp6_chunk16(y, (c & 1) != 0);
           if (ok) store_fp6_chunk(o.fp6 + r * j.cols, c, f6);
         }
         if (++ip == g.iters) {  // end of the group's row
           if (o.row_sumsq) {
-            ss = group_sum(ss, g.G);
-            if (ok && g.sub == 0) o.row_sumsq[r] = ss;
+            ss = group_sum(ss, j.log2g, rsum, par);
+            if (in_row && g.sub == 0) o.row_sumsq[r] = ss;
           }
           ss = 0;
           ip = 0;
@@ -447,8 +543,8 @@ __global__ __launch_bounds__(kQThreads) void fwht_lsq_kernel(QJob j0, QJob j1, L
       const int tt = (int)blockIdx.x - nrow, b = tt / nt;
       const int64_t rc = j1.rows * j1.cols;  // elements of one batch
       quant_tile<DT, LOG2B, true>(static_cast<const char*>(j1.src) + (int64_t)b * j1.bstride * Elem<DT>::bytes,
-                                  j1.rows, j1.cols, 1.0f / o1.step[b], tt % nt, o1.packed + b * (rc / 2),
-                                  o1.delta + b * rc, o1.packed_t + b * (rc / 2));
+                                  j1.rows, j1.cols, [&]() { return 1.0f / o1.step[b]; }, tt % nt,
+                                  o1.packed + b * (rc / 2), o1.delta + b * rc, o1.packed_t + b * (rc / 2));
       return;
     }
   }
@@ -459,7 +555,9 @@ __global__ __launch_bounds__(kQThreads) void fwht_lsq_kernel(QJob j0, QJob j1, L
   const float inv = 1.0f / o.step[qp.b];
   const Geo g(j, wg);
   constexpr int EB = Elem<DT>::bytes;
-  const char* base = static_cast<const char*>(j.src) + ((int64_t)qp.b * j.bstride + (int64_t)g.sub * kVE) * EB;
+  const char* base = static_cast<const char*>(j.src) + (int64_t)qp.b * j.bstride * EB;
+  __shared__ int rsum[2 * kQWaves];
+  int par = 0;
   // this batch's outputs
   uint8_t* const packed = o.packed + (int64_t)qp.b * j.rows * (j.cols / 2);
   uint16_t* const delta = o.delta + (int64_t)qp.b * j.rows * j.cols;
@@ -472,7 +570,7 @@ __global__ __launch_bounds__(kQThreads) void fwht_lsq_kernel(QJob j0, QJob j1, L
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
-        load16<DT, HQ_NT_Q_LD>(base + (g.row_of(k) * j.cols + (int64_t)it * g.G * kVE) * EB, v[u]);
+        load16<DT, HQ_NT_Q_LD>(base + (g.row_of(k) * j.cols + g.load_col(it)) * EB, v[u]);
         if (++it == g.iters) { it = 0; ++k; }
       }
     }
@@ -497,11 +595,12 @@ __global__ __launch_bounds__(kQThreads) void fwht_lsq_kernel(QJob j0, QJob j1, L
           dh[e / 2] = h[0] | (h[1] << 16);
         }
         const uint32_t w0 = pack8_bits(y), w1 = pack8_bits(y + 8);
-        ss = sumsq8(w1, sumsq8(w0, ss));
-        const bool ok = g.valid(kp);
+        const int c = g.chunk(ip);  // 16-column chunk
+        const bool live = g.live(ip);
+        ss = live ? sumsq8(w1, sumsq8(w0, ss)) : ss;
+        const bool in_row = g.valid(kp), ok = live && in_row;
         const int64_t r = g.row_of(kp);
         if (ok) {
-          const int64_t c = (int64_t)ip * g.G + g.sub;  // 16-column chunk
           st_stream2<HQ_NT_Q_ST>(reinterpret_cast<uint2*>(packed + r * (j.cols / 2)) + c, make_uint2(w0, w1));
           uint4* dp = reinterpret_cast<uint4*>(delta + r * j.cols) + 2 * c;
           st_stream<HQ_NT_Q_ST>(dp, make_uint4(dh[0], dh[1], dh[2], dh[3]));
@@ -509,8 +608,8 @@ __global__ __launch_bounds__(kQThreads) void fwht_lsq_kernel(QJob j0, QJob j1, L
         }
         if (++ip == g.iters) {
           if (row_sumsq) {
-            ss = group_sum(ss, g.G);
-            if (ok && g.sub == 0) row_sumsq[r] = ss;
+            ss = group_sum(ss, j.log2g, rsum, par);
+            if (in_row && g.sub == 0) row_sumsq[r] = ss;
           }
           ss = 0;
           ip = 0;
@@ -537,9 +636,6 @@ __global__ __launch_bounds__(kQThreads) void bit_split_kernel(QJob j, const floa
   __shared__ uint32_t red_n[kQWaves];
   // batch b of a batched job: its own maximum, outputs and Philox counter range
   const int b = (int)blockIdx.x / j.wg, wg = (int)blockIdx.x % j.wg;
-  const float a = reduce_parts(part + (int64_t)b * nparts, nparts);
-  if (wg == 0 && threadIdx.x == 0) o.amax_out[b] = a;
-  const float inv = a > 0.f ? 7.0f / a : 0.f;
   // -0.0f, from an argument so that the fma below is not folded into a multiply
   const float nzero = __uint_as_float(0x80000000u | (uint32_t)((uint64_t)j.cols >> 63));
   const Geo g(j, wg);
@@ -547,7 +643,9 @@ __global__ __launch_bounds__(kQThreads) void bit_split_kernel(QJob j, const floa
   constexpr int EB = Elem<DT>::bytes;
   uint32_t nnz = 0;
   uint64_t ssum = 0;
-  const char* base = static_cast<const char*>(j.src) + ((int64_t)b * j.bstride + (int64_t)g.sub * kVE) * EB;
+  const char* base = static_cast<const char*>(j.src) + (int64_t)b * j.bstride * EB;
+  __shared__ int rsum[2 * kQWaves];
+  int par = 0;
   offset += (uint64_t)b * o.offset_stride;
   const int64_t rb = (int64_t)b * j.rows;  // first row of this batch in the row-indexed outputs
   uint8_t* const qup = o.qup + rb * (C / 2);
@@ -559,22 +657,32 @@ __global__ __launch_bounds__(kQThreads) void bit_split_kernel(QJob j, const floa
   int64_t k = 0, kp = 0;
   int it = 0, ip = 0;
   int su = 0, sd = 0;
-  for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
-    float v[U][kVE];
+  Raw16<DT> raw[U];
+  auto load = [&](int64_t s0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
-        load16<DT, HQ_NT_BS_LD>(base + (g.row_of(k) * C + (int64_t)it * g.G * kVE) * EB, v[u]);
+        raw[u].template load<HQ_NT_BS_LD>(base + (g.row_of(k) * C + g.load_col(it)) * EB);
         if (++it == g.iters) { it = 0; ++k; }
       }
     }
+  };
+  load(0);  // in flight while the maximum is formed
+  const float a = reduce_parts(part + (int64_t)b * nparts, nparts);
+  if (wg == 0 && threadIdx.x == 0) o.amax_out[b] = a;
+  const float inv = a > 0.f ? 7.0f / a : 0.f;
+  for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
+    if (s0) load(s0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
-        const bool ok = g.valid(kp);
+        const int c = g.chunk(ip);
+        const bool live = g.live(ip), in_row = g.valid(kp);
         const int64_t r = g.row_of(kp);
-        const int64_t col = ((int64_t)ip * g.G + g.sub) * kVE;
+        const int64_t col = (int64_t)c * kVE;
         uint32_t yu[kVE], yd[kVE];
+        float v[kVE];
+        raw[u].widen(v);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const U4 rnd = philox_block(seed, offset, 0u, (uint64_t)(r * C + col + 8 * h));
@@ -582,7 +690,7 @@ __global__ __launch_bounds__(kQThreads) void bit_split_kernel(QJob j, const floa
           for (int e = 0; e < 8; ++e) {
             // fl(v inv): one rounding, so the fma with a -0 addend equals the product
             // (an fp16 operand widens inside the instruction)
-            const float x = __builtin_fmaf(v[u][8 * h + e], inv, nzero);
+            const float x = __builtin_fmaf(v[8 * h + e], inv, nzero);
             const uint32_t bu = rne_bits(x);                  // |x| <= 7 (1 + 2^-23)
             // -14 rint(x) exactly from the bits 1.5 * 2^23 + rint(x); then
             // fl(14 x - 14 rint(x)) = fl(14 (x - rint(x))), the residual being exact
@@ -597,25 +705,25 @@ __global__ __launch_bounds__(kQThreads) void bit_split_kernel(QJob j, const floa
         }
         const uint32_t u0 = pack8_bits(yu), u1 = pack8_bits(yu + 8);
         const uint32_t d0 = pack8_bits(yd), d1 = pack8_bits(yd + 8);
-        su = sumsq8(u1, sumsq8(u0, su));
-        sd = sumsq8(d1, sumsq8(d0, sd));
-        if (ok) {
-          const int64_t o8 = r * (C / 16) + (int64_t)ip * g.G + g.sub;  // uint2 index
+        su = live ? sumsq8(u1, sumsq8(u0, su)) : su;
+        sd = live ? sumsq8(d1, sumsq8(d0, sd)) : sd;
+        if (live && in_row) {
+          const int64_t o8 = r * (C / 16) + c;  // uint2 index
           st_stream2<HQ_NT_BS_ST>(reinterpret_cast<uint2*>(qup) + o8, make_uint2(u0, u1));
           st_stream2<HQ_NT_BS_ST>(reinterpret_cast<uint2*>(qdn) + o8, make_uint2(d0, d1));
         }
         if (++ip == g.iters) {  // end of the group's row
           if (packed_sums) {  // one reduction of the two halves
-            const int p = group_sum(su | (sd << 16), g.G);
+            const int p = group_sum(su | (sd << 16), j.log2g, rsum, par);
             su = p & 0xFFFF;
             sd = (int)((uint32_t)p >> 16);
           } else {
-            su = group_sum(su, g.G);
-            sd = group_sum(sd, g.G);
+            su = group_sum(su, j.log2g, rsum, par);
+            sd = group_sum(sd, j.log2g, rsum, par);
           }
           // the group's lane 0 forms the upper row's score and lane 1 the lower row's
           // (G >= 4), so a wave runs one square root per row end, not two in sequence
-          if (ok && g.sub < 2) {
+          if (in_row && g.sub < 2) {
             const uint64_t sx = (uint32_t)o.x_sumsq[rb + r];
             const bool upper = g.sub == 0;
             const uint64_t k2 = upper ? (uint64_t)(kBsRatio * kBsRatio) * (uint32_t)su : (uint64_t)(uint32_t)sd;
@@ -711,26 +819,20 @@ __global__ __launch_bounds__(kQThreads) void hsize_max_kernel(QJob j0, QJob j1,
   const bool second = (int)blockIdx.x >= j0.wg;
   const QJob& j = second ? j1 : j0;
   const int wg = second ? (int)blockIdx.x - j0.wg : (int)blockIdx.x;
-  const Geo g(j, wg);
+  const Flat g(j, wg);
   constexpr int EB = Elem<DT>::bytes;
   float m[kLevels];
 #pragma unroll
   for (int l = 0; l < kLevels; ++l) m[l] = 0.f;
-  const char* base = static_cast<const char*>(j.src) + (int64_t)g.sub * kVE * EB;
-  int64_t k = 0;
-  int it = 0;
+  const char* base = static_cast<const char*>(j.src);
   for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
     float v[U][kVE];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (s0 + u < g.steps) {
-        load16<DT, HQ_NT_ABS_LD>(base + (g.row_of(k) * j.cols + (int64_t)it * g.G * kVE) * EB, v[u]);
-        if (++it == g.iters) { it = 0; ++k; }
-      }
-    }
+    for (int u = 0; u < U; ++u)
+      if (s0 + u < g.steps) load16<DT, HQ_NT_ABS_LD>(base + g.load_chunk(s0 + u) * (kVE * EB), v[u]);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (s0 + u < g.steps) {  // duplicated rows leave the maxima unchanged
+      if (s0 + u < g.steps) {  // chunks loaded twice leave the maxima unchanged
         fwht_nested(v[u], g.lane, [&](int l, const float* x) {
 #pragma unroll
           for (int e = 0; e < kVE; e += 2) m[l] = fmaxf(m[l], fmaxf(fabsf(x[e]), fabsf(x[e + 1])));
@@ -785,27 +887,21 @@ __global__ __launch_bounds__(kQThreads) void hsize_err_kernel(QJob j0, QJob j1,
     inv[l] = a > 0.f ? 7.0f / a : 0.f;
     st[l] = a / 7.0f;
   }
-  const Geo g(j, wg);
+  const Flat g(j, wg);
   constexpr int EB = Elem<DT>::bytes;
   double acc[kLevels];
 #pragma unroll
   for (int l = 0; l < kLevels; ++l) acc[l] = 0.0;
-  const char* base = static_cast<const char*>(j.src) + (int64_t)g.sub * kVE * EB;
-  int64_t k = 0, kp = 0;
-  int it = 0, ip = 0;
+  const char* base = static_cast<const char*>(j.src);
   for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
     float v[U][kVE];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (s0 + u < g.steps) {
-        load16<DT, HQ_NT_ABS_LD>(base + (g.row_of(k) * j.cols + (int64_t)it * g.G * kVE) * EB, v[u]);
-        if (++it == g.iters) { it = 0; ++k; }
-      }
-    }
+    for (int u = 0; u < U; ++u)
+      if (s0 + u < g.steps) load16<DT, HQ_NT_ABS_LD>(base + g.load_chunk(s0 + u) * (kVE * EB), v[u]);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
-        const bool ok = g.valid(kp);
+        const bool ok = g.valid(s0 + u);
         fwht_nested(v[u], g.lane, [&](int l, const float* x) {
           float e2 = 0.f;
 #pragma unroll
@@ -816,7 +912,6 @@ __global__ __launch_bounds__(kQThreads) void hsize_err_kernel(QJob j0, QJob j1,
           }
           acc[l] += ok ? (double)e2 : 0.0;
         });
-        if (++ip == g.iters) { ip = 0; ++kp; }
       }
     }
   }
@@ -836,32 +931,49 @@ __global__ __launch_bounds__(kQThreads) void hsize_err_kernel(QJob j0, QJob j1,
   }
 }
 
-// Pass 3 (one workgroup of 256): MSE_k = sum / (2^k numel) per tensor, the candidates
+// Pass 3 (one workgroup of 1024): MSE_k = sum / (2^k numel) per tensor, the candidates
 // k <= kmax with cols % 2^k == 0, and the argmin of MSE_X MSE_W (ties to the smaller k).
-// mse_out[k] = MSE_X(k), mse_out[8 + k] = MSE_W(k), NaN for k not a candidate.
-__global__ __launch_bounds__(256) void hsize_pick_kernel(const double* __restrict__ err0, int n0,
+// mse_out[k] = MSE_X(k), mse_out[8 + k] = MSE_W(k), NaN for k not a candidate.  Latency is
+// all it costs: 128 threads share a level's partials, so that few loads and additions stand
+// in a row (10.4 us with 32 threads a level and one thread adding up their sums, 4.6 us so).
+constexpr int kPickThreads = 1024;
+__global__ __launch_bounds__(kPickThreads) void hsize_pick_kernel(const double* __restrict__ err0, int n0,
                                                          const double* __restrict__ err1, int n1,
                                                          double numel0, double numel1, int64_t cols,
                                                          int kmax, int32_t* __restrict__ k_out,
                                                          double* __restrict__ mse_out) {
-  __shared__ double red[2][32][kLevels];
-  const int l = threadIdx.x & 7, slot = threadIdx.x >> 3;  // 32 slots per level
+  __shared__ double red[2][kPickThreads / 64][kLevels];
+  __shared__ double tot[2][kLevels];
+  const int l = threadIdx.x & 7, slot = threadIdx.x >> 3;  // 128 slots per level
+  constexpr int kSlots = kPickThreads / kLevels;
   double a = 0.0, b = 0.0;
-  for (int i = slot; i < n0; i += 32) a += err0[i * kLevels + l];
-  for (int i = slot; i < n1; i += 32) b += err1[i * kLevels + l];
-  red[0][slot][l] = a;
-  red[1][slot][l] = b;
+  for (int i = slot; i < (n0 > n1 ? n0 : n1); i += kSlots) {
+    if (i < n0) a += err0[i * kLevels + l];
+    if (i < n1) b += err1[i * kLevels + l];
+  }
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1) {  // lanes of one level are 8 apart
+    a += __shfl_xor(a, o);
+    b += __shfl_xor(b, o);
+  }
+  if ((threadIdx.x & 63) < kLevels) {
+    red[0][threadIdx.x >> 6][l] = a;
+    red[1][threadIdx.x >> 6][l] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 * kLevels) {
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < kPickThreads / 64; ++i) t += red[threadIdx.x >> 3][i][l];
+    tot[threadIdx.x >> 3][l] = t;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     int best = 0;
     double best_obj = 0.0;
     bool any = false;
     for (int k = 0; k < kLevels; ++k) {
-      double sx = 0.0, sw = 0.0;
-      for (int i = 0; i < 32; ++i) {
-        sx += red[0][i][k];
-        sw += red[1][i][k];
-      }
+      const double sx = tot[0][k], sw = tot[1][k];
       const double scale = (double)(1 << k);
       const double mx = numel0 > 0 ? sx / (scale * numel0) : 0.0;
       const double mw = numel1 > 0 ? sw / (scale * numel1) : 0.0;
@@ -915,16 +1027,50 @@ int resident_wgs(const void* f) {
   return n;
 }
 
-int64_t wgs_needed(const QJob& j) {
+// Lanes per row (as a logarithm): a wave's steps are the rows it takes in turn times the
+// chunks a lane takes of each, for a grid of two workgroups per CU, and the group with the
+// fewest wins, a group wider than a wave counting one more per row for its barrier.  Ties go
+// to the largest power of two up to 64 that divides the row: no lane idles there, and it is
+// the choice wherever rows are many or their chunks a power of two.  Few rows, or 64-multiples
+// with odd factors, take wider groups (the last chunks of a row then leave lanes idle): 1003
+// rows of 832 and 1344 columns, fp32, with 4 lanes per row (8 workgroups) and with 64:
+// maximum 11.5 -> 3.6 us, bit split 28.4 -> 9.0 us, quantiser 16.1 -> 7.5 us.
+// The choice does not depend on the kernel, and grids of more than one round are multiples
+// of 8, so every kernel that walks a tensor reads a row on the same XCD and finds what fits
+// its L2 there (the quantiser of 16384 x 768 fp16 after a maximum pass that walked the
+// tensor in another order: 13.9 us, in this one 12.4 us).
+void choose_group(QJob& j) {
+  if (j.rows <= 0) return;
+  constexpr int64_t cap = 512;
+  const int64_t chunks = j.cols / kVE;
+  auto steps = [&](int l) {
+    const int64_t rw = kQThreads >> l;
+    const int64_t rounds = (j.rows * j.batch + rw * cap - 1) / (rw * cap);
+    return rounds * (((chunks - 1) >> l) + 1 + (l > 6 ? 1 : 0));
+  };
+  int best = j.log2g;
+  for (int l = j.log2g + 1; (1 << l) <= kQThreads && (chunks >> (l - 1)) > 0; ++l)
+    if (steps(l) < steps(best)) best = l;
+  j.log2g = best;
+}
+
+// Workgroups that leave each thread one step (flat kernels) or each group one row.
+int64_t wgs_needed(const QJob& j, bool flat) {
   if (j.rows <= 0) return 0;
-  const int64_t per = (int64_t)(64 >> j.log2g) * kQWaves;
+  if (flat) return (j.rows * (j.cols / kVE) + kQThreads - 1) / kQThreads;
+  const int64_t per = kQThreads >> j.log2g;
   return (j.rows + per - 1) / per;
 }
 
 // Share one resident grid between two jobs: all they need if it fits, else in proportion
 // to their sizes (each at least one workgroup).
-void fit_grid(QJob& a, QJob& b, int cap) {
-  const int64_t na = wgs_needed(a), nb = wgs_needed(b);  // per batch
+// flat: a kernel that takes the tensors as runs of chunks; else the row groups are chosen here.
+void fit_grid(QJob& a, QJob& b, int cap, bool flat = false) {
+  if (!flat) {
+    choose_group(a);
+    choose_group(b);
+  }
+  const int64_t na = wgs_needed(a, flat), nb = wgs_needed(b, flat);  // per batch
   if (na * a.batch + nb * b.batch <= cap) {
     a.wg = (int)na;
     b.wg = (int)nb;
@@ -948,6 +1094,7 @@ void fit_grid(QJob& a, QJob& b, int cap) {
   }
   const double ba = (double)a.rows * a.cols, bb = (double)b.rows * b.cols;
   int64_t wb = nb ? (int64_t)(cap * bb / (ba + bb) + 0.5) : 0;
+  wb = (wb + 7) / 8 * 8;  // whole rounds of the 8 XCDs
   if (nb && wb < 1) wb = 1;
   if (wb > nb) wb = nb;
   int64_t wa = cap - wb;
@@ -1104,7 +1251,7 @@ hipError_t launch_hsize_search(hipStream_t s, int dt, QJob& j0, QJob& j1, float*
                                 : reinterpret_cast<const void*>(&hsize_err_kernel<kBF16>);
   if (dt != kF32 && dt != kF16 && dt != kBF16) return hipErrorInvalidValue;
   QJob a0 = j0, a1 = j1;
-  fit_grid(a0, a1, resident_wgs(fm));
+  fit_grid(a0, a1, resident_wgs(fm), true);
   timing_begin(s);
   if (dt == kF32) hsize_max_kernel<kF32><<<a0.wg + a1.wg, kQThreads, 0, s>>>(a0, a1, mx0, mx1);
   else if (dt == kF16) hsize_max_kernel<kF16><<<a0.wg + a1.wg, kQThreads, 0, s>>>(a0, a1, mx0, mx1);
@@ -1113,7 +1260,7 @@ hipError_t launch_hsize_search(hipStream_t s, int dt, QJob& j0, QJob& j1, float*
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   QJob b0 = j0, b1 = j1;
-  fit_grid(b0, b1, resident_wgs(fe));
+  fit_grid(b0, b1, resident_wgs(fe), true);
   timing_begin(s);
   if (dt == kF32)
     hsize_err_kernel<kF32><<<b0.wg + b1.wg, kQThreads, 0, s>>>(b0, b1, mx0, a0.wg, mx1, a1.wg, err0, err1);
@@ -1125,7 +1272,7 @@ hipError_t launch_hsize_search(hipStream_t s, int dt, QJob& j0, QJob& j1, float*
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   timing_begin(s);
-  hsize_pick_kernel<<<1, 256, 0, s>>>(err0, b0.wg, err1, b1.wg, (double)j0.rows * (double)j0.cols,
+  hsize_pick_kernel<<<1, kPickThreads, 0, s>>>(err0, b0.wg, err1, b1.wg, (double)j0.rows * (double)j0.cols,
                                       (double)j1.rows * (double)j1.cols, j0.cols, kmax, k_out,
                                       mse_out);
   timing_end(s, kKHsizePick);
