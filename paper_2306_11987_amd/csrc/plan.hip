@@ -9,11 +9,9 @@
 //   1. inclusion probabilities by the clamp-and-rescale loop of App. A.2 with sum p = B,
 //      in exact integers.  Thresholds S/R only fall from one round to the next, so the
 //      rows clamped after a round are exactly {c > 0 : R c >= S} for that round's (R, S):
-//      a round needs that set's count and sum, and no per-row state (the 1024-thread
-//      build takes them from scores binned once, the 256-thread one from a pass over
-//      the scores).  If no more
-//      than B rows have c > 0, every such row has p = 1 (the "keep rows with norm > 0"
-//      rule of the paper's implementation, App. A.6);
+//      a round needs that set's count and sum, one pass over the scores, and no per-row
+//      state.  If no more than B rows have c > 0, every such row has p = 1 (the
+//      "keep rows with norm > 0" rule of the paper's implementation, App. A.6);
 //   2. upper rows are kept iff non-zero; a lower row with p* < 1 gets p~ = 2^-e >= p*, the
 //      smallest power of two (e <= 4, e <= 2 if the token's upper row is non-zero), and is
 //      kept iff u16 < 2^(16-e) (Philox stream 1), weight m/p~ = 2^e;
@@ -41,8 +39,6 @@ namespace {
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanThreadsSmall = 256;
 
-constexpr int kPlanRegs = 32;  // scores per thread kept in registers (2N <= 32 x threads)
-
 // Sum of a 32-bit value over the wave (every lane gets it): DPP adds inside each row of
 // 16 lanes (swap neighbours, swap pairs, mirror halves, mirror the row), then the four row
 // sums read as scalars.  Needs every lane of the wave active.
@@ -55,6 +51,15 @@ __device__ __forceinline__ uint32_t wave_sum_u32_dpp(uint32_t v) {
          (uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
 }
 
+// The same over the first 16 lanes only.
+__device__ __forceinline__ uint32_t row16_sum_u32_dpp(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
+}
+
 // 64-bit wave sum as three 21-bit limbs (64 limbs of at most 22 bits stay below 2^28, so
 // each limb sum is exact in 32 bits), recombined modulo 2^64.
 __device__ __forceinline__ uint64_t wave_sum_u64_dpp(uint64_t v) {
@@ -65,36 +70,40 @@ __device__ __forceinline__ uint64_t wave_sum_u64_dpp(uint64_t v) {
   return (uint64_t)s0 + ((uint64_t)s1 << 21) + ((uint64_t)s2 << 42);
 }
 
-// Two block-wide sums with one barrier.  red holds 2 WAVES words; callers alternate
-// between two such buffers, so that a buffer is written again only after the barrier
-// that follows every read of it.
-template <int WAVES>
-__device__ __forceinline__ void block_sum2_u64(uint64_t& a, uint64_t& b, uint64_t* red) {
-  a = wave_sum_u64_dpp(a);
-  b = wave_sum_u64_dpp(b);
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6] = a;
-    red[WAVES + (threadIdx.x >> 6)] = b;
-  }
-  __syncthreads();
-  a = 0;
-  b = 0;
-#pragma unroll
-  for (int i = 0; i < WAVES; ++i) {
-    a += red[i];
-    b += red[WAVES + i];
-  }
+__device__ __forceinline__ uint64_t row16_sum_u64_dpp(uint64_t v) {
+  constexpr uint64_t kM21 = (1ull << 21) - 1;
+  const uint32_t s0 = row16_sum_u32_dpp((uint32_t)(v & kM21));
+  const uint32_t s1 = row16_sum_u32_dpp((uint32_t)((v >> 21) & kM21));
+  const uint32_t s2 = row16_sum_u32_dpp((uint32_t)(v >> 42));
+  return (uint64_t)s0 + ((uint64_t)s1 << 21) + ((uint64_t)s2 << 42);
 }
 
-// Score bins of the 1024-thread sampler's clamp-and-rescale rounds: 32 per octave (the
-// position of the leading one, then the next five bits), so the bin never decreases with
-// the score: a score in a bin above the threshold's bin is at least the threshold, one in
-// a bin below it is smaller, and only the threshold's own bin needs comparisons.
-constexpr int kHistBins = 1024;
-__device__ __forceinline__ int score_bin(uint32_t c) {  // c > 0
-  const int e = 31 - __builtin_clz(c);
-  const uint32_t m = e >= 5 ? (c >> (e - 5)) : (c << (5 - e));
-  return e * 32 + (int)(m & 31u);
+// Inclusive prefix sum over the wave by DPP (shifts inside each row of 16 lanes, then the
+// rows' last lanes broadcast to the rows after them).  Needs every lane of the wave active.
+__device__ __forceinline__ uint32_t wave_scan_u32_dpp(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);  // row_shr 1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);  // row_shr 2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);  // row_shr 4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);  // row_shr 8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast 15, rows 1 and 3
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast 31, rows 2 and 3
+  return v;
+}
+
+// floor(S / R) for 0 < R < 2^18 and S < 2^50, and the remainder: the quotient from a
+// reciprocal refined to double precision is off by at most one, which the exact remainder
+// corrects (a dozen instructions in a row instead of the 64-bit division's hundred and fifty).
+__device__ __forceinline__ uint64_t quotient(uint64_t S, uint32_t R, uint64_t& rem) {
+  const double d = (double)R;
+  double r = __builtin_amdgcn_rcp(d);
+  r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+  r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+  uint64_t q = (uint64_t)((double)S * r);
+  int64_t m = (int64_t)(S - q * R);
+  if (m < 0) { --q; m += R; }
+  if (m >= (int64_t)R) { ++q; m -= R; }
+  rem = (uint64_t)m;
+  return q;
 }
 
 // 8 consecutive words from p + t0 (n8 of them valid, the rest 0).
@@ -109,26 +118,39 @@ __device__ __forceinline__ void load8u(const uint32_t* p, int t0, int n8, uint32
   }
 }
 
-template <int kPlanThreads>
-__global__ __launch_bounds__(kPlanThreads) void lss_plan_kernel(
+// What bounds it is latency: one workgroup (per problem) and a chain of dependent loads,
+// rounds and barriers on one CU.  So:
+//   - the loads of a problem of up to 16 tokens per thread are issued before the first is
+//     used (8 consecutive tokens per thread and group, as 16-byte pieces);
+//   - a clamp-and-rescale round is one pass over registers that counts by scalar popcounts
+//     of the comparison masks; what is the same for all (the sums over the waves, the
+//     quotient S / R) is formed by the first wave alone, the others waiting: in every wave
+//     it cost four times its instructions, 16 waves sharing four SIMDs;
+//   - R c >= S and R c 2^e <= S are comparisons of c with quotients formed once;
+//   - the kept list is compacted in LDS and leaves in whole lines (8 scattered words a thread
+//     before).
+// N = 128 (five rounds): 11.3 -> 9.4 us; N = 16384, lognormal rows, budget N (no round):
+// 10.2 -> 7.5 us, Pareto rows (eight rounds): 37.9 -> 25.6 us.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void lss_plan_kernel(
     const int32_t* __restrict__ sumsq_up, const uint32_t* __restrict__ scores, int64_t pitch,
     const uint4* __restrict__ parts, int nparts, int N, int64_t B, uint64_t seed,
     uint64_t offset, uint8_t* __restrict__ w_up, uint8_t* __restrict__ w_dn,
     int32_t* __restrict__ kept, int32_t* __restrict__ n_kept, uint64_t offset_stride) {
-  constexpr int kPlanWaves = kPlanThreads / kWave;
-  __shared__ uint64_t red[4 * kPlanWaves];  // two buffers of block_sum2_u64
-  __shared__ int wtot[kPlanWaves];
-  // the 1024-thread sampler runs its rounds on binned scores (below): per-bin counts (then
-  // the end of each bin's bucket), first slots and sums (then the sums of the bins above),
-  // and the non-zero scores bucketed by bin, highest bin first (128 KB of LDS)
-  constexpr bool kHist = kPlanThreads == 1024;
-  constexpr int kHistCap = kHist ? kPlanRegs * kPlanThreads : 1;
-  static_assert(!kHist || kHistBins == kPlanThreads, "one bin per thread in the scan");
-  __shared__ uint32_t h_end[kHist ? kHistBins : 1];
-  __shared__ uint32_t h_off[kHist ? kHistBins : 1];
-  __shared__ uint64_t h_sum[kHist ? kHistBins : 1];
-  __shared__ uint32_t h_score[kHistCap];
-  __shared__ uint64_t h_rs[2];
+  constexpr int WAVES = THREADS / kWave;
+  static_assert(WAVES <= 16, "the waves' sums are combined by one row of 16 lanes");
+  struct Ctl {
+    uint64_t T, F;  // ceil(S / R) and floor(S / R) of the round, saturated where R = 0
+    int done, all;
+  };
+  struct WaveSum {
+    uint32_t n;
+    uint64_t sum;
+  };
+  __shared__ Ctl ctl;
+  __shared__ WaveSum red[WAVES];
+  __shared__ uint32_t wtot[WAVES];    // kept tokens of each wave, two groups packed
+  __shared__ int32_t kept_s[16 * THREADS];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   {  // workgroup b samples batch b of a batched call (its own inputs, outputs and counters)
     const int64_t bt = blockIdx.x;
@@ -141,262 +163,234 @@ __global__ __launch_bounds__(kPlanThreads) void lss_plan_kernel(
     n_kept += bt;
     offset += (uint64_t)bt * offset_stride;
   }
-
-  // totals of the bit-split workgroups: non-zero rows and the score sum
-  uint64_t nz = 0, st = 0;
-  for (int i = tid; i < nparts; i += kPlanThreads) {
-    const uint4 p = parts[i];
-    nz += p.x;
-    st += ((uint64_t)p.z << 32) | p.y;
-  }
-  block_sum2_u64<kPlanWaves>(nz, st, red);  // buffer 0; the rounds start on buffer 1
-  const uint64_t S_all = st;
-  const bool all_nonzero_kept = (int64_t)nz <= B;
-
-  // App. A.2 clamp-and-rescale (uniform across the block); each round is one pass over
-  // the scores, held in registers when they fit
-  uint64_t S = S_all;
-  int64_t R = B;
-  if (!all_nonzero_kept) {
-    const int64_t n2 = 2 * (int64_t)N;
-    const bool in_regs = n2 <= (int64_t)kPlanRegs * kPlanThreads;
-    uint32_t cs[kPlanRegs];
-#pragma unroll
-    for (int j = 0; j < kPlanRegs; ++j) {
-      const int64_t i = tid + (int64_t)j * kPlanThreads;
-      cs[j] = (in_regs && i < n2) ? scores[i < N ? i : pitch + (i - N)] : 0u;
-    }
-    if (kHist && in_regs) {
-      // The same rounds on binned scores.  One pass builds each bin's count and sum, a
-      // scan from the top bin down gives the count and sum of all bins above each bin,
-      // and a second pass places the scores in per-bin buckets.  A round then takes the
-      // bins above its threshold's bin from the scan and compares only the threshold's
-      // own bin, in one wave: the rounds' counts and sums, and so their sequence, are
-      // those of the full passes.
-      for (int b = tid; b < kHistBins; b += kPlanThreads) {
-        h_end[b] = 0;
-        h_sum[b] = 0;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kPlanRegs; ++j)
-        if (cs[j]) {
-          const int b = score_bin(cs[j]);
-          atomicAdd(&h_end[b], 1u);
-          atomicAdd(reinterpret_cast<unsigned long long*>(&h_sum[b]), (unsigned long long)cs[j]);
-        }
-      __syncthreads();
-      const int hb = kHistBins - 1 - tid;  // thread t scans bin 1023 - t
-      const uint32_t c0 = h_end[hb];
-      const uint64_t s0 = h_sum[hb];
-      uint32_t ci = c0;
-      uint64_t si = s0;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t cy = __shfl_up(ci, o);
-        const uint32_t lo = __shfl_up((uint32_t)si, o), hi = __shfl_up((uint32_t)(si >> 32), o);
-        if (lane >= o) {
-          ci += cy;
-          si += ((uint64_t)hi << 32) | lo;
-        }
-      }
-      // red: its last reads (the totals above) came before the barriers since
-      if (lane == 63) {
-        red[wid] = ci;
-        red[kPlanWaves + wid] = si;
-      }
-      __syncthreads();
-      uint32_t cpre = 0;
-      uint64_t spre = 0;
-#pragma unroll
-      for (int i = 0; i < kPlanWaves; ++i)
-        if (i < wid) {
-          cpre += (uint32_t)red[i];
-          spre += red[kPlanWaves + i];
-        }
-      const uint32_t above = cpre + ci - c0;  // scores in the bins above hb
-      h_off[hb] = above;
-      h_end[hb] = above;  // the bucket's fill cursor, then its end
-      h_sum[hb] = spre + si - s0;
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kPlanRegs; ++j)
-        if (cs[j]) h_score[atomicAdd(&h_end[score_bin(cs[j])], 1u)] = cs[j];
-      __syncthreads();
-      if (wid == 0) {  // the rounds, in one wave (uniform)
-        int64_t k = 0, Rr = B;
-        uint64_t Sr = S_all;
-        // the count grows every round that does not stop, so at most 2N + 1 rounds run;
-        // the bound only makes that certain
-        for (int64_t round = 0; round <= n2; ++round) {
-          Rr = B - k;
-          const uint64_t T = Sr == 0 ? 1 : Rr <= 0 ? ~uint64_t(0) : (Sr + (uint64_t)Rr - 1) / (uint64_t)Rr;
-          uint64_t cnt = 0, sum = 0;
-          if (T <= 0xFFFFFFFFull) {  // else no score reaches it
-            const uint32_t T32 = (uint32_t)T;
-            const int b = score_bin(T32);
-            const uint32_t end = h_end[b];
-            uint32_t n = 0;
-            uint64_t sm = 0;
-            for (uint32_t i = h_off[b] + lane; i < end; i += 64) {
-              const uint32_t c = h_score[i];
-              if (c >= T32) {
-                ++n;
-                sm += c;
-              }
-            }
-            cnt = (uint64_t)h_off[b] + wave_sum_u32_dpp(n);
-            sum = h_sum[b] + wave_sum_u64_dpp(sm);
-          }
-          if ((int64_t)cnt == k) break;  // nothing newly clamped
-          k = (int64_t)cnt;
-          Sr = S_all - sum;
-        }
-        if (lane == 0) {
-          h_rs[0] = (uint64_t)Rr;
-          h_rs[1] = Sr;
-        }
-      }
-      __syncthreads();
-      R = (int64_t)h_rs[0];
-      S = h_rs[1];
-    } else {  // full passes (256-thread sampler, or 2N beyond the register-held scores)
-      int64_t k = 0;
-      int par = 1;
-      for (;;) {
-        R = B - k;
-        // R c >= S  <=>  c >= ceil(S / R) for integers and R > 0: one division per round
-        // instead of a 64-bit product per score.  S = 0 admits every non-zero score (as
-        // R c >= 0 does); R = 0 with S > 0 admits none.
-        const uint64_t T = S == 0 ? 1 : R <= 0 ? ~uint64_t(0) : (S + (uint64_t)R - 1) / (uint64_t)R;
-        // T >= 1, so c >= T implies c > 0; a threshold past the 32-bit scores admits none
-        const uint32_t T32 = (uint32_t)T;
-        uint32_t n = 0;
-        uint64_t sum = 0;
-        if (T > 0xFFFFFFFFull) {  // uniform
-        } else if (in_regs) {
-#pragma unroll
-          for (int j = 0; j < kPlanRegs; ++j) {
-            const uint32_t c = cs[j];
-            const bool in = c >= T32;
-            n += in;
-            sum += in ? c : 0u;
-          }
-        } else {  // eight loads in flight per thread
-          for (int64_t i0 = tid; i0 < n2; i0 += 8 * (int64_t)kPlanThreads) {
-            uint32_t c8[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const int64_t i = i0 + (int64_t)u * kPlanThreads;
-              c8[u] = i < n2 ? scores[i < N ? i : pitch + (i - N)] : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const bool in = c8[u] >= T32;
-              n += in;
-              sum += in ? c8[u] : 0u;
-            }
-          }
-        }
-        uint64_t cnt = n;
-        block_sum2_u64<kPlanWaves>(cnt, sum, red + 2 * kPlanWaves * par);
-        par ^= 1;
-        if ((int64_t)cnt == k) break;  // nothing newly clamped
-        k = (int64_t)cnt;
-        S = S_all - sum;
-      }
-    }
-  }
-
-  // weights, masks and compaction of one round: 8 consecutive tokens per thread
-  int base = 0;
+  const uint32_t* cup = scores;
   const uint32_t* cdn = scores + pitch;
   const uint32_t* sup = reinterpret_cast<const uint32_t*>(sumsq_up);
-  auto round = [&](int t0, int n8, const uint32_t su[8], const uint32_t cd[8]) {
+
+  // up to 16 tokens per thread (two groups of 8 consecutive ones) stay in registers
+  const bool in_regs = N <= 16 * THREADS;
+  int t0[2] = {0, 0}, n8[2] = {0, 0};
+  uint32_t su[2][8], cu[2][8], cd[2][8];
+  if (in_regs) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      t0[r] = r * 8 * THREADS + 8 * tid;
+      n8[r] = t0[r] < N ? (N - t0[r] < 8 ? N - t0[r] : 8) : 0;
+      load8u(cdn, t0[r], n8[r], cd[r]);
+      load8u(sup, t0[r], n8[r], su[r]);
+      load8u(cup, t0[r], n8[r], cu[r]);
+    }
+  }
+
+  // App. A.2 clamp-and-rescale: k rows clamped so far, R = B - k and S the sum of the
+  // others' scores.  R c >= S  <=>  c >= ceil(S / R) for integers and R > 0; S = 0 admits
+  // every non-zero score, R = 0 with S > 0 none.  The first wave holds the state.
+  uint64_t S_all = 0, S = 0;
+  int64_t k = 0;
+  uint64_t rT = 1, rF = 0;  // ceil(S / R) and floor(S / R)
+  auto set_round = [&]() {
+    const int64_t R = B - k;
+    if (S == 0) {
+      rT = 1;
+      rF = 0;
+    } else if (R > 0) {
+      uint64_t rem;
+      rF = quotient(S, (uint32_t)R, rem);
+      rT = rF + (rem ? 1 : 0);
+    } else {
+      rT = rF = ~uint64_t(0);
+    }
+  };
+  if (wid == 0) {  // totals of the bit-split workgroups: non-zero rows and the score sum
+    uint32_t nz = 0;
+    uint64_t st = 0;
+#pragma unroll 8
+    for (int i = lane; i < nparts; i += 64) {
+      const uint4 p = parts[i];
+      nz += p.x;
+      st += ((uint64_t)p.z << 32) | p.y;
+    }
+    nz = wave_sum_u32_dpp(nz);
+    S = S_all = wave_sum_u64_dpp(st);
+    const bool all = (int64_t)nz <= B;  // T = 1 clamps every non-zero row
+    if (!all) set_round();
+    if (lane == 0) ctl = {rT, rF, 0, all};
+  }
+  __syncthreads();
+  const bool all_nonzero_kept = ctl.all;
+  if (!all_nonzero_kept) {
+    const int64_t n2 = 2 * (int64_t)N;
+    // upper scores of each group of tokens not counted for good yet: their number in the
+    // wave; thresholds only fall, so once all of them are clamped they stay so, and the
+    // count and sum carry over (most upper rows are zero, the others large)
+    uint32_t up[2] = {0u, 0u}, n_up = 0;
+    uint64_t s_up = 0;
+    if (in_regs) {
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) up[r] += (uint32_t)__builtin_popcountll(__ballot(cu[r][j] != 0));
+    }
+    auto pass = [&](uint64_t T, uint32_t& n, uint64_t& sum) {  // n: of the wave, sum: of the thread
+      // T >= 1, so c >= T implies c > 0; a threshold past the 32-bit scores admits none
+      const uint32_t T32 = (uint32_t)T;
+      n = n_up;
+      sum = s_up;
+      if (T > 0xFFFFFFFFull) return;  // uniform; no upper row has been clamped then
+      auto take = [&](uint32_t c, uint32_t& m, uint64_t& v) {
+        const bool in = c >= T32;
+        m += (uint32_t)__builtin_popcountll(__ballot(in));
+        v += in ? c : 0u;
+      };
+      if (in_regs) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          if (r == 1 && N <= 8 * THREADS) break;  // uniform: no second group
+#pragma unroll
+          for (int j = 0; j < 8; ++j) take(cd[r][j], n, sum);
+          if (up[r]) {
+            uint32_t m = 0;
+            uint64_t v = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) take(cu[r][j], m, v);
+            n += m;
+            sum += v;
+            if (m == up[r]) {
+              up[r] = 0;
+              n_up += m;
+              s_up += v;
+            }
+          }
+        }
+      } else {  // eight loads in flight per thread
+        for (int64_t i0 = wid * 64; i0 < n2; i0 += 8 * (int64_t)THREADS) {  // uniform
+          uint32_t c8[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int64_t i = i0 + lane + (int64_t)u * THREADS;
+            c8[u] = i < n2 ? scores[i < N ? i : pitch + (i - N)] : 0u;
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) take(c8[u], n, sum);
+        }
+      }
+    };
+    auto advance = [&](int64_t cnt, uint64_t sum) -> bool {  // first wave: the round's totals
+      if (cnt == k) return true;  // nothing newly clamped
+      S = S_all - sum;
+      k = cnt;
+      set_round();
+      return false;
+    };
+    if (N <= 8 * kWave) {  // the first wave holds every token: no barrier
+      if (wid == 0) {
+        for (;;) {
+          uint32_t n;
+          uint64_t sum;
+          pass(rT, n, sum);
+          if (advance(n, wave_sum_u64_dpp(sum))) break;
+        }
+        if (lane == 0) ctl = {rT, rF, 1, 0};
+      }
+      __syncthreads();
+    } else {
+      for (;;) {
+        uint32_t n;
+        uint64_t sum;
+        pass(ctl.T, n, sum);
+        sum = wave_sum_u64_dpp(sum);
+        if (lane == 0) red[wid] = {n, sum};
+        __syncthreads();
+        if (wid == 0) {
+          const WaveSum p = lane < WAVES ? red[lane] : WaveSum{0u, 0u};
+          const bool done = advance(row16_sum_u32_dpp(p.n), row16_sum_u64_dpp(p.sum));
+          if (lane == 0) ctl = {rT, rF, done, 0};
+        }
+        __syncthreads();
+        if (ctl.done) break;  // read before the barrier that precedes its next write
+      }
+    }
+  }
+  // a lower row is clamped (p = 1) for c >= T; else R c 2^i <= S  <=>  c <= floor(F / 2^i)
+  const uint64_t T = ctl.T, F = ctl.F;
+  const uint32_t T32 = T > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)T;
+  const bool none = T > 0xFFFFFFFFull;  // no 32-bit score reaches T
+  uint32_t Fi[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) Fi[i] = (F >> (i + 1)) > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)(F >> (i + 1));
+
+  // weights and masks of 8 consecutive tokens; returns the mask of the kept ones
+  auto weigh = [&](int t, int n, const uint32_t* su8, const uint32_t* cd8) -> uint32_t {
     // Bernoulli draws only when some row has p < 1 (uniform over the workgroup)
     const U4 rnd = all_nonzero_kept ? U4{0u, 0u, 0u, 0u}
-                                    : philox_block(seed, offset, 1u, (uint64_t)(t0 > 0 ? t0 : 0));
+                                    : philox_block(seed, offset, 1u, (uint64_t)t);
     uint32_t wu8[2] = {0u, 0u}, wd8[2] = {0u, 0u};
     uint32_t keepmask = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const uint32_t wu = su[j] ? 1u : 0u;
+      const uint32_t c = cd8[j], wu = su8[j] ? 1u : 0u;
       uint32_t wd = 0;
-      if (cd[j]) {
-        const uint64_t rc = (uint64_t)R * cd[j];
-        if (all_nonzero_kept || rc >= S) {
-          wd = 1;
-        } else {
-          // e = min(cap, largest e with rc 2^e <= S), here 0 < rc < S: from the bit lengths
-          // of rc and S and one comparison
-          const int cap = wu ? 2 : 4;
-          int e = cap;
-          if (rc != 0) {
-            const int e0 = __builtin_clzll(rc) - __builtin_clzll(S);
-            const int m = (rc << e0) <= S ? e0 : e0 - 1;
-            e = m < cap ? m : cap;
-          }
-          wd = (u16_of(rnd, j) < (1u << (16 - e))) ? (1u << e) : 0u;
-        }
+      if (!none && c >= T32) {  // T >= 1: c > 0
+        wd = 1;
+      } else if (c) {
+        uint32_t e = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e += c <= Fi[i] ? 1u : 0u;
+        const uint32_t cap = wu ? 2u : 4u;
+        e = e < cap ? e : cap;
+        wd = (u16_of(rnd, j) < (1u << (16 - e))) ? (1u << e) : 0u;
       }
-      if (j >= n8) wd = 0;
       wu8[j >> 2] |= wu << (8 * (j & 3));
       wd8[j >> 2] |= wd << (8 * (j & 3));
       if (wu + wd) keepmask |= 1u << j;
     }
-    if (n8 == 8) {
-      *reinterpret_cast<uint2*>(w_up + t0) = make_uint2(wu8[0], wu8[1]);
-      *reinterpret_cast<uint2*>(w_dn + t0) = make_uint2(wd8[0], wd8[1]);
+    if (n == 8) {
+      *reinterpret_cast<uint2*>(w_up + t) = make_uint2(wu8[0], wu8[1]);
+      *reinterpret_cast<uint2*>(w_dn + t) = make_uint2(wd8[0], wd8[1]);
     } else {
-      for (int j = 0; j < n8; ++j) {
-        w_up[t0 + j] = (uint8_t)(wu8[j >> 2] >> (8 * (j & 3)));
-        w_dn[t0 + j] = (uint8_t)(wd8[j >> 2] >> (8 * (j & 3)));
+      for (int j = 0; j < n; ++j) {
+        w_up[t + j] = (uint8_t)(wu8[j >> 2] >> (8 * (j & 3)));
+        w_dn[t + j] = (uint8_t)(wd8[j >> 2] >> (8 * (j & 3)));
       }
     }
-    // block-wide exclusive scan of the per-thread keep counts
-    const int nkeep = __builtin_popcount(keepmask);
-    int x = nkeep;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wtot[wid] = x;
-    __syncthreads();
-    int pre = 0, total = 0;
-#pragma unroll
-    for (int i = 0; i < kPlanWaves; ++i) {
-      pre += (i < wid) ? wtot[i] : 0;
-      total += wtot[i];
-    }
-    __syncthreads();
-    int pos = base + pre + x - nkeep;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if ((keepmask >> j) & 1) kept[pos++] = t0 + j;
-    base += total;
+    return keepmask;
   };
-  if (N <= 2 * 8 * kPlanThreads) {
-    // both rounds' inputs in one round trip to memory
-    uint32_t su[2][8], cd[2][8];
-    int t0[2], n8[2];
+  // The kept tokens of one or two groups, in order, into kept[base ...]: the counts of both
+  // packed in one scan (at most 8 THREADS = 8192 each), the tokens placed in LDS.
+  int base = 0;
+  auto compact = [&](int ta, uint32_t ka, int tb, uint32_t kb) {
+    const uint32_t mine = __builtin_popcount(ka) | (__builtin_popcount(kb) << 16);
+    const uint32_t incl = wave_scan_u32_dpp(mine);
+    if (lane == 63) wtot[wid] = incl;
+    __syncthreads();
+    const uint32_t w = lane < WAVES ? wtot[lane] : 0u;
+    const uint32_t before = wave_sum_u32_dpp(lane < wid ? w : 0u), total = wave_sum_u32_dpp(w);
+    const uint32_t excl = before + incl - mine;
+    const int na = (int)(total & 0xFFFFu), nb = (int)(total >> 16);
+    int pa = (int)(excl & 0xFFFFu), pb = na + (int)(excl >> 16);
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      t0[r] = r * 8 * kPlanThreads + 8 * tid;
-      n8[r] = t0[r] < N ? (N - t0[r] < 8 ? N - t0[r] : 8) : 0;
-      load8u(sup, t0[r], n8[r], su[r]);
-      load8u(cdn, t0[r], n8[r], cd[r]);
+    for (int j = 0; j < 8; ++j) {
+      if ((ka >> j) & 1) kept_s[pa++] = ta + j;
+      if ((kb >> j) & 1) kept_s[pb++] = tb + j;
     }
-    round(t0[0], n8[0], su[0], cd[0]);
-    if (N > 8 * kPlanThreads) round(t0[1], n8[1], su[1], cd[1]);
+    __syncthreads();
+    for (int i = tid; i < na + nb; i += THREADS) kept[base + i] = kept_s[i];
+    base += na + nb;
+  };
+  if (in_regs) {
+    const uint32_t ka = weigh(t0[0], n8[0], su[0], cd[0]);
+    const uint32_t kb = N > 8 * THREADS ? weigh(t0[1], n8[1], su[1], cd[1]) : 0u;
+    compact(t0[0], ka, t0[1], kb);
   } else {
-    for (int r0 = 0; r0 < N; r0 += 8 * kPlanThreads) {
+    for (int r0 = 0; r0 < N; r0 += 8 * THREADS) {
       const int t = r0 + 8 * tid;
       const int n = t < N ? (N - t < 8 ? N - t : 8) : 0;
-      uint32_t su[8], cd[8];
-      load8u(sup, t, n, su);
-      load8u(cdn, t, n, cd);
-      round(t, n, su, cd);
+      uint32_t su8[8], cd8[8];
+      load8u(sup, t, n, su8);
+      load8u(cdn, t, n, cd8);
+      const uint32_t ka = weigh(t, n, su8, cd8);
+      compact(t, ka, 0, 0u);
+      __syncthreads();  // the LDS copy is read before the next group fills it
     }
   }
   if (tid == 0) *n_kept = base;
