@@ -169,11 +169,12 @@ size_t grads_bytes(int64_t N, int64_t D, int64_t C, bool dx, bool dw) {
   return (dx ? dx_bytes(N, D, C) : 0) + (dw ? dw_bytes(N, D, C) : 0);
 }
 // learned-step-size mode: per-workgroup sums of acc * delta of the dX and dW epilogues
-int64_t lsq_parts_dx(int64_t N, int64_t D, int64_t C) {
-  return gemm_epi_parts(N, D, gemm_splits(N, D, C, false, true));
+// (k: the Hadamard block; an upper bound without one)
+int64_t lsq_parts_dx(int64_t N, int64_t D, int64_t C, int k = -1) {
+  return gemm_epi_parts(N, D, gemm_splits(N, D, C, false, true), 0, k);
 }
-int64_t lsq_parts_dw(int64_t N, int64_t D, int64_t C) {
-  return gemm_epi_parts(C, D, gemm_splits(C, D, rup(N, kPad), false, true));
+int64_t lsq_parts_dw(int64_t N, int64_t D, int64_t C, int k = -1) {
+  return gemm_epi_parts(C, D, gemm_splits(C, D, rup(N, kPad), false, true), 0, k);
 }
 size_t lsq_parts_bytes(int64_t N, int64_t D, int64_t C, bool dx, bool dw) {
   return (dx ? al(8 * lsq_parts_dx(N, D, C)) : 0) + (dw ? al(8 * lsq_parts_dw(N, D, C)) : 0);
@@ -397,7 +398,7 @@ struct BmmWs {
   int64_t tiles_dx, tiles_dw;
 };
 BmmWs bmm_ws_dims(int64_t B, int64_t N, int64_t M, int64_t P) {
-  return {B + kBatchWgSlack, rup(N, kPad), gemm_epi_parts(N, M, 1), gemm_epi_parts(P, M, 1)};
+  return {B + kBatchWgSlack, rup(N, kPad), gemm_epi_parts(N, M, 1, B, -1), gemm_epi_parts(P, M, 1, B, -1)};
 }
 size_t bmm_bwd_bytes(int64_t B, int64_t N, int64_t M, int64_t P, bool dq, bool dk) {
   const BmmWs d = bmm_ws_dims(B, N, M, P);
@@ -579,8 +580,8 @@ hqlss_status do_grads(const lss_plan_t* p, const hqlss_saved_t* sv, void* dX, vo
     // g(s) = 1 / sqrt(Q_P numel) with Q_P = 7 (App. A.3)
     const double gx = 1.0 / std::sqrt(7.0 * (double)N * (double)D);
     const double gw = 1.0 / std::sqrt(7.0 * (double)C * (double)D);
-    HQ_TRY(launch_lsq_step_grad(s, px, px ? lsq_parts_dx(N, D, C) : 0, pw,
-                                pw ? lsq_parts_dw(N, D, C) : 0, p->amax_g, lsq->step,
+    HQ_TRY(launch_lsq_step_grad(s, px, px ? lsq_parts_dx(N, D, C, k) : 0, pw,
+                                pw ? lsq_parts_dw(N, D, C, k) : 0, p->amax_g, lsq->step,
                                 lsq->step + 1, k, gx, gw, dstep, dstep + 1));
   }
   return HQLSS_OK;

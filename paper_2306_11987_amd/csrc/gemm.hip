@@ -338,10 +338,24 @@ int gemm_splits(int64_t M, int64_t N, int64_t K, bool a_int4, bool b_int4) {
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int64_t stages = (K + kKS - 1) / kKS;
   if (2 * tiles >= slots || stages < 16) return 1;
+  // A split costs its partials and the reduction, 5 us and more: with an eighth of the CUs
+  // holding a 128 x 128 tile it is of use from about 24 stages (kernel times, split and not:
+  // 2048^3, 16 stages, forward 21.1 and 12.0 us; N = 2048, 1024 -> 2048, 16 stages, dX 13.7
+  // and 11.6; N = 1024, 1024 -> 4096, 32 stages, dX 13.5 and 15.6).
+  if (stages < 24 && ((M + 127) / 128) * ((N + 127) / 128) >= 32) return 1;
   int64_t s = slots / tiles;        // all splits resident at once (no second round)
   const int64_t smax = stages / 8;  // keep >= 8 stages per split
   if (s > smax) s = smax;
   return (int)(s < 1 ? 1 : s);
+}
+
+bool gemm_small(int64_t M, int64_t N, int splits, int64_t batch) {
+  // At most 64 tiles of 128 x 128, i.e. one 64 x 64 workgroup per CU: kernel times, the
+  // 128-wide tiles first, N = 512, 1024 x 1024, b = 32: forward 6.2 -> 4.7 us, dX 7.1 -> 5.4;
+  // 1024^3 (64 tiles): forward 6.3 -> 5.0, dX 7.0 -> 5.6; 1003 x 832 -> 1344: forward (88
+  // tiles) 6.4 -> 6.8; 1024 x 1024 -> 4096: forward (256 tiles) 7.6 -> 13.0.
+  if (splits > 1 || batch > 0 || g_bn_override) return false;
+  return ((M + 127) / 128) * ((N + 127) / 128) <= 64;
 }
 
 size_t gemm_partial_bytes(int64_t M, int64_t N, int splits) {
@@ -351,6 +365,9 @@ size_t gemm_partial_bytes(int64_t M, int64_t N, int splits) {
 hipError_t launch_gemm(hipStream_t s, int epi, int dt, bool a_int4, bool b_int4, const GemmArgs& g,
                        int splits, int32_t* partial) {
   if (!b_int4) return hipErrorInvalidValue;
+  if (epi != kEpiAcc && (a_int4 || (epi != kEpiDw && epi != kEpiDwL) || g.a_kmajor) &&
+      gemm_small(g.M, g.N, splits, g.batch))
+    return launch_gemm_small(s, epi, dt, a_int4, g);
   if (a_int4) {
     if (epi == kEpiFwd) return run_dt<true, kEpiFwd>(s, dt, g, splits, partial, kKGemmFwd);
     if (epi == kEpiAcc) return run<true, kEpiAcc, kF32>(s, g, splits, partial, kKGemmAcc);
@@ -368,7 +385,11 @@ hipError_t launch_gemm(hipStream_t s, int epi, int dt, bool a_int4, bool b_int4,
   return hipErrorInvalidValue;
 }
 
-int64_t gemm_epi_parts(int64_t M, int64_t N, int splits) {
+int64_t gemm_epi_parts(int64_t M, int64_t N, int splits, int64_t batch, int log2b) {
+  if (gemm_small(M, N, splits, batch)) {
+    const int64_t bn = gemm_small_bn(log2b);
+    return ((N + bn - 1) / bn) * ((M + kSmallBM - 1) / kSmallBM);
+  }
   if (splits <= 1) {
     const int64_t bm = tile_m<false>();
     const int64_t bn = grad_bn(M, N, splits);  // as gemm_b chooses

@@ -21,6 +21,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 constexpr int kBN = 256;  // workgroup tile width (n)
 constexpr int kNarrowBN = 64;  // tile width of the gradient GEMMs for outputs <= 64 wide
 constexpr int kMidBN = 128;    // tile width of gradient GEMMs with few 256-wide tiles
+constexpr int kSmallBM = 64;   // tile height of GEMMs with few tiles (gemm_small.hip)
 // Split-K gradient GEMMs wider than 64 columns run 128-wide tiles: twice the tiles, so
 // about half the splits fill the device and half the int32 partials are written and
 // summed (and a GEMM whose 128-wide tiles fill one round alone is not split at all).
@@ -61,8 +62,11 @@ struct Cfg {
   static constexpr int A_BYTES = BM * RA, B_BYTES = BN * RB, STAGE = A_BYTES + B_BYTES;
   static constexpr int A_BPW = A_BYTES / 1024 / WAVES, B_BPW = B_BYTES / 1024 / WAVES;
   static constexpr int DMA = A_BPW + B_BPW;  // 1 KB LDS-DMA loads per wave per stage
-  static constexpr int OCC = BM == 128 ? 2 : 1;  // workgroups per CU
-  static constexpr int NBUF = (F6 && BM == 256) ? HQLSS_F6_NBUF256 : (OCC == 2 && !A4) ? 2 : 3;
+  static constexpr int OCC = BM == 128 ? 2 : 1;  // workgroups per CU (at least)
+  // 64-row tiles run where a CU holds a workgroup or two: with nothing else to hide a load
+  // behind, four or five stages of loads stay in flight
+  static constexpr int NBUF = BM == kSmallBM ? (STAGE <= 12 * 1024 ? 6 : 4)
+                              : (F6 && BM == 256) ? HQLSS_F6_NBUF256 : (OCC == 2 && !A4) ? 2 : 3;
   static constexpr int LDS_MAIN = NBUF * STAGE;
   static constexpr int SHIFT = F6 ? 0 : (A4 ? 4 : 0) + 4;
   static_assert(A_BYTES % (1024 * WAVES) == 0 && B_BYTES % (1024 * WAVES) == 0, "DMA split");
@@ -207,6 +211,19 @@ __device__ __forceinline__ void wait_vm_lgkm0() {
   __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | (7 << 4));
 }
 
+// Waits until at most min(Q, later) stages of DMA loads each are in flight (and every LDS
+// operation of this wave is done).
+template <int Q, int DMA>
+__device__ __forceinline__ void wait_later(int later) {
+  if constexpr (Q == 0) {
+    wait_vm_lgkm0<0>();
+  } else {
+    static_assert(Q * DMA < 64, "the load counter");
+    if (later >= Q) wait_vm_lgkm0<Q * DMA>();
+    else wait_later<Q - 1, DMA>(later);
+  }
+}
+
 // alpha = fl(fl(s1 s2) / denom); an operand flagged in steps_mask is a step itself,
 // otherwise a tensor maximum a with s = fl(a / 7).
 __device__ __forceinline__ float scale_of(const GemmArgs& g) {
@@ -242,7 +259,7 @@ __device__ __forceinline__ double block_sum_f64(double v, double* red) {
 constexpr int kF6Dx = 1, kF6Dw = 2;
 // TRA (int8 x INT4 only): A is stored k-major, A[k][m] with pitch lda and its m positions
 // K-interleaved in groups of 8 (the dX operand A_T read as the dW operand A_T^T).  A stage
-// of it lands in LDS as 128 k rows of BM m bytes, and the gfx950 transposing read
+// of it lands in LDS as 128 k rows of BM m bytes (BM = 64 or 128), and the gfx950 transposing read
 // ds_read_b64_tr_b8 forms the k-contiguous MFMA fragments out of it: in each group of 16
 // lanes, byte b of lane j comes from byte j % 8 of the 8 bytes addressed by lane
 // 2 b + j / 8.  Output row m' of the tile is then the interleaved position, i.e. row
@@ -268,8 +285,14 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
                          : (BM / 4 * E_PITCH <= SMEM) ? BM / 4 : BM / 8;
   static_assert(E_ROWS >= 32 && E_ROWS * E_PITCH <= SMEM, "epilogue staging");
   static_assert(!(F6 && LSQ), "the learned-step epilogues run on the int8 route");
-  static_assert(!TRA || (!A4 && !F6 && !ROWMAP && C_::RA == 128 && C_::KS == 128),
-                "k-major A: int8 A, 128-byte rows of 128 k per stage, plain output rows");
+  static_assert(!TRA || (!A4 && !F6 && !ROWMAP && C_::RA == 128 && C_::KS == 128 && (BM == 64 || BM == 128)),
+                "k-major A: int8 A, 128 k per stage, plain output rows");
+  // bytes of an A row in LDS and its 16-byte chunks; a k-major row's chunks are XOR-swizzled
+  // by its position among 8 (the transposing reads take 8 rows x 2 chunks at once: with 8
+  // chunks a row, any permutation by row spreads them; with 4, rows 4 apart share banks, and
+  // the upper four take the other pair of chunks)
+  constexpr int RAL = TRA ? BM : C_::RA, CPAL = RAL / 16;
+  auto tra_swz = [](int r) -> int { return BM == 128 ? (r & 7) : ((r >> 1) & 2); };
   // result row of tile row gm (k-major A: the K-interleaved position gm)
   auto res_row = [](int64_t gm) -> int64_t { return TRA ? ((gm & ~int64_t(7)) | nu8((int)(gm & 7))) : gm; };
   __shared__ __attribute__((aligned(1024))) uint8_t smem[SMEM];
@@ -345,9 +368,9 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
   int ca[C_::A_BPW], cb[C_::B_BPW];
 #pragma unroll
   for (int x = 0; x < C_::A_BPW; ++x) {
-    const int r = (wid * C_::A_BPW + x) * (1024 / C_::RA) + lane / C_::CPA;
+    const int r = (wid * C_::A_BPW + x) * (1024 / RAL) + lane / CPAL;
     if constexpr (TRA) {  // r: k row of the stage; chunks past M re-read the last 16 m
-      const int c = (lane % C_::CPA) ^ (r & 7);
+      const int c = (lane % CPAL) ^ tra_swz(r);
       int64_t col = m0 + c * 16;
       col = col + 16 <= M ? col : M - 16;
       ca[x] = c * 16;
@@ -470,7 +493,7 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
       // of the fragment's 32; that row's chunks are swizzled by its k % 8 = nu8(j / 2)
       const int j = lane & 15, q = lane >> 4, kr = nu8(j >> 1);
       const int chunk = (wm * C_::WM + 32 * i) / 16 + (q & 1);
-      offa[i] = (32 * (q >> 1) + kr) * C_::RA + ((chunk ^ kr) << 4) + 8 * (j & 1);
+      offa[i] = (32 * (q >> 1) + kr) * RAL + ((chunk ^ tra_swz(kr)) << 4) + 8 * (j & 1);
     }
   }
 #pragma unroll
@@ -505,9 +528,9 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
           // k step 2 pp + h: bytes 0-7 of the fragment from k rows 64 pp + 16 h + 0..7 (+ 32 fg),
           // bytes 8-15 from the next 8 rows
           typedef __attribute__((address_space(3))) v2i lds_v2i;
-          const uint8_t* p = sa + offa[i] + (64 * pp + 16 * h) * C_::RA;
+          const uint8_t* p = sa + offa[i] + (64 * pp + 16 * h) * RAL;
           const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(lds_void*)p);
-          const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(lds_void*)(p + 8 * C_::RA));
+          const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(lds_void*)(p + 8 * RAL));
           ra[slot][h][i] = make_uint4((uint32_t)lo[0], (uint32_t)lo[1], (uint32_t)hi[0], (uint32_t)hi[1]);
           continue;
         }
@@ -542,7 +565,7 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
   // Learned-step epilogues read this tile's deltas (2 B per output) after the main loop.
   // The deltas are fetched into the caches during the main loop by LDS-DMA loads into a
   // 1 KB sink (no registers held): each lane touches one 128-byte line of one row.
-  constexpr bool PREFETCH = LSQ && HQLSS_LSQ_PREFETCH;
+  constexpr bool PREFETCH = LSQ && HQLSS_LSQ_PREFETCH && BM != kSmallBM;
   // with two stage buffers every stage wait drains all loads, the prefetch included
   static_assert(!PREFETCH || C_::NBUF == 2, "partial stage waits would not count the prefetch");
   __shared__ __attribute__((aligned(1024))) uint8_t pf_sink[PREFETCH ? 1024 : 16];
@@ -565,10 +588,7 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
   };
   auto stage_ready = [&](int st) {  // this wave's loads of stage st landed, then all waves'
     // loads of later stages may stay in flight: min(NBUF - 2, nst - 1 - st) of them
-    const int later = nst - 1 - st;
-    if (C_::NBUF >= 4 && later >= 2) wait_vm_lgkm0<2 * C_::DMA>();
-    else if (C_::NBUF >= 3 && later >= 1) wait_vm_lgkm0<C_::DMA>();
-    else wait_vm_lgkm0<0>();
+    wait_later<C_::NBUF - 2, C_::DMA>(nst - 1 - st);
     __builtin_amdgcn_s_barrier();
     if (st + C_::NBUF - 1 < nst) issue(st + C_::NBUF - 1);
     if (st == 0) prefetch_delta();

@@ -164,6 +164,11 @@ void gemm_set_split_override(int splits);
 void gemm_set_tile_override(int bn);
 hipError_t launch_gemm(hipStream_t s, int epi, int dt, bool a_int4, bool b_int4, const GemmArgs& g,
                        int splits, int32_t* partial);
+// The same products on 64-row tiles, for grids too small to fill the device with 128-row ones
+// (launch_gemm takes this route by itself; never split along K or batched).
+bool gemm_small(int64_t M, int64_t N, int splits, int64_t batch);
+hipError_t launch_gemm_small(hipStream_t s, int epi, int dt, bool a_int4, const GemmArgs& g);
+int gemm_small_bn(int log2b);  // tile width of its gradient products
 // Tile widths the launchers choose (forward, gradients), and the split-K reduction with the
 // epilogue of `epi` on its own (kEpiAcc, kEpiFwd, kEpiDx, kEpiDw).
 int gemm_fwd_bn(int64_t M, int64_t N, int splits, int64_t batch);
@@ -199,8 +204,8 @@ hipError_t launch_fp6_build(hipStream_t s, int dt, const uint8_t* qup, const uin
                             uint8_t* x_dw, void* dX);
 // Number of ds_part entries a kEpiDxL / kEpiDwL launch of this shape writes (one per
 // workgroup: of the GEMM, or of the reduction after split-K; every entry is written, 0 by
-// workgroups without rows).
-int64_t gemm_epi_parts(int64_t M, int64_t N, int splits);
+// workgroups without rows).  log2b < 0: an upper bound over the blocks.
+int64_t gemm_epi_parts(int64_t M, int64_t N, int splits, int64_t batch, int log2b);
 // Step-size gradients from the partial sums (one workgroup, fixed order):
 // dstep_x = gx * (s_up / 14) s_w 2^-k * sum(px), dstep_w = gw * (s_up / 14) s_x 2^-k *
 // sum(pw), s_up = fl(*amax_g / 7), s_x = *step_x, s_w = *step_w; an entry with no partials
