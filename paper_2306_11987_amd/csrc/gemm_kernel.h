@@ -158,19 +158,32 @@ __device__ __forceinline__ void fwht_lane(int* v, int lane) {
 // G operand panels of one side and 64 / G of the other in that XCD's L2, instead of the
 // two rows by all columns of the plain order.  The chunk's partial first and last rows
 // come after its whole rows, in the plain order.
+// a / b for a >= 0, b > 0 (uniform): a quotient below 2^22 from the reciprocal is off by at
+// most one, corrected by its remainder; it takes a third of the instructions of the integer
+// division, and a workgroup divides five times before its first load.
+__device__ __forceinline__ int quick_div(int a, int b) {
+  if (a >= (1 << 22)) return a / b;
+  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+  const int r = a - q * b;
+  q += r >= b ? 1 : 0;
+  q -= r < 0 ? 1 : 0;
+  return __builtin_amdgcn_readfirstlane(q);
+}
+
 template <int G>
 __device__ __forceinline__ int grouped_tile(int j, int s, int len, int tiles_n) {
-  const int rf = (s + tiles_n - 1) / tiles_n, rl = (s + len) / tiles_n;
+  const int rf = quick_div(s + tiles_n - 1, tiles_n), rl = quick_div(s + len, tiles_n);
   if (rl - rf < 2) return s + j;
   const int R = rl - rf, nfull = R * tiles_n, head = rf * tiles_n - s;
   if (j < nfull) {
     const int nfg = tiles_n / G;
     if (j < nfg * R * G) {
-      const int g = j / (R * G), inner = j - g * (R * G);
+      const int g = quick_div(j, R * G), inner = j - g * (R * G);
       return (rf + inner / G) * tiles_n + g * G + inner % G;
     }
     const int rem = j - nfg * R * G, gl = tiles_n - nfg * G;
-    return (rf + rem / gl) * tiles_n + nfg * G + rem % gl;
+    const int rr = quick_div(rem, gl);
+    return (rf + rr) * tiles_n + nfg * G + (rem - rr * gl);
   }
   if (j < nfull + head) return s + (j - nfull);
   return rl * tiles_n + (j - nfull - head);
@@ -188,20 +201,28 @@ __device__ __forceinline__ bool tile_of(int T, int tiles_n, int& tm, int& tn) {
   } else if (b >= T) {
     return false;
   }
-  tm = L / tiles_n;
-  tn = L % tiles_n;
+  tm = quick_div(L, tiles_n);
+  tn = L - tm * tiles_n;
   return true;
 }
 
-// 16-byte LDS-DMA load (global_load_lds_dwordx4): each lane's 16 bytes at g land at
-// lds_base + 16 * lane.  Issued as inline assembly with a memory clobber: the compiler
+// 16-byte LDS-DMA load (global_load_lds_dwordx4): each lane's 16 bytes at base + off land at
+// lds_base + 16 * lane.  The base is the tile's and stage's (scalar), the offset the lane's
+// within the tile (below 2^31: at most 128 or 256 rows of up to 2^24 bytes), so that a load
+// takes no vector arithmetic.  Issued as inline assembly with a memory clobber: the compiler
 // keeps it in program order with every other memory access, but does not treat it as a
 // pending LDS write; it would otherwise wait for every such load before any later LDS
 // read, including the loads just issued for a later stage.  The stage pipeline waits for
 // exactly the loads each stage needs.
-__device__ __forceinline__ void dma16(const void* g, void* lds_base) {
+__device__ __forceinline__ void dma16(const uint8_t* base, uint32_t off, void* lds_base) {
   const uint32_t l = (uint32_t)(uintptr_t)(lds_void*)lds_base;
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(l) : "memory");
+  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(l) : "memory");
+}
+
+// The same from a lane's own address.
+__device__ __forceinline__ void dma16_at(const void* p, void* lds_base) {
+  const uint32_t l = (uint32_t)(uintptr_t)(lds_void*)lds_base;
+  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(p), "{m0}"(l) : "memory");
 }
 
 // s_waitcnt: vector-memory count <= n, LDS count 0 (gfx9 encoding: vmcnt [3:0] and
@@ -335,15 +356,17 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
     return;
   }
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  // the scale is read up front so that its latency hides behind the main loop
   float alpha = 0.f;
-  if constexpr (EPI == kEpiFwd) {
-    // fl(alpha 2^-SHIFT * fl(acc)) == fl(alpha * fl(acc >> SHIFT)): acc is a multiple of
-    // 2^SHIFT and both scalings by powers of two are exact
-    alpha = scale_of(g) * (1.0f / (float)(1 << C_::SHIFT));
-  } else if constexpr (GRAD) {
-    alpha = scale_of(g);
-  }
+  auto read_scale = [&]() {
+    if constexpr (EPI == kEpiFwd) {
+      // fl(alpha 2^-SHIFT * fl(acc)) == fl(alpha * fl(acc >> SHIFT)): acc is a multiple of
+      // 2^SHIFT and both scalings by powers of two are exact
+      alpha = scale_of(g) * (1.0f / (float)(1 << C_::SHIFT));
+    } else if constexpr (GRAD) {
+      alpha = scale_of(g);
+    }
+  };
+  if constexpr (F6 && F6K != 0) read_scale();
   int64_t K = g.K;
   if (g.k_dev) K = ((int64_t)*g.k_dev + 127) / 128 * 128;
   // FP6 dX tiles holding upper-row tokens (rows below *m2_dev) run two K passes, first over
@@ -356,41 +379,52 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
   }
   // split-K range of this workgroup (whole stages)
   const int nst_all = two ? 2 * npass : (int)((K + C_::KS - 1) / C_::KS);
-  const int per = (nst_all + nsplit - 1) / nsplit;
+  const int per = nsplit > 1 ? quick_div(nst_all + nsplit - 1, nsplit) : nst_all;
   const int st0 = zsplit * per;
   const int nst = max(0, min(nst_all, st0 + per) - st0);
   const int64_t Ka = F6 ? K : A4 ? K / 2 : K, Kb = F6 ? K : K / 2;  // row extents in bytes
 
-  // per-lane source pointers of this wave's DMA blocks (stage 0 of this split); rows past
-  // the end re-read the last row (their results are never stored)
-  const uint8_t* pa[C_::A_BPW];
-  const uint8_t* pb[C_::B_BPW];
+  // tile bases and per-lane offsets of this wave's DMA blocks (stage 0 of this split); rows
+  // past the end re-read the last row (their results are never stored)
+  const uint8_t* const baseA = static_cast<const uint8_t*>(g.A) +
+                               (TRA ? (int64_t)st0 * C_::KS * g.lda + m0
+                                    : m0 * g.lda + (F6 ? 0 : (int64_t)st0 * C_::RA));
+  const uint8_t* const baseB = static_cast<const uint8_t*>(g.B) + n0 * g.ldb + (F6 ? 0 : (int64_t)st0 * C_::RB);
+  const uint32_t lda = (uint32_t)g.lda, ldb = (uint32_t)g.ldb;
+  const int m_left = (int)(M - m0 < BM ? M - m0 : BM), n_left = (int)(g.N - n0 < BN ? g.N - n0 : BN);
+  uint32_t oa[C_::A_BPW], ob[C_::B_BPW];
   int ca[C_::A_BPW], cb[C_::B_BPW];
 #pragma unroll
   for (int x = 0; x < C_::A_BPW; ++x) {
     const int r = (wid * C_::A_BPW + x) * (1024 / RAL) + lane / CPAL;
     if constexpr (TRA) {  // r: k row of the stage; chunks past M re-read the last 16 m
       const int c = (lane % CPAL) ^ tra_swz(r);
-      int64_t col = m0 + c * 16;
-      col = col + 16 <= M ? col : M - 16;
       ca[x] = c * 16;
-      pa[x] = static_cast<const uint8_t*>(g.A) + ((int64_t)st0 * C_::KS + r) * g.lda + col;
+      oa[x] = (uint32_t)r * lda + (uint32_t)min(c * 16, m_left - 16);
       continue;
     }
     const int c = (lane % C_::CPA) ^ swz<C_::RA>(r);
-    int64_t gm = m0 + r;
-    gm = gm < M ? gm : M - 1;
     ca[x] = c * 16;
-    pa[x] = static_cast<const uint8_t*>(g.A) + gm * g.lda + (F6 ? 0 : (int64_t)st0 * C_::RA) + c * 16;
+    oa[x] = (uint32_t)min(r, m_left - 1) * lda + c * 16;
   }
 #pragma unroll
   for (int x = 0; x < C_::B_BPW; ++x) {
     const int s = (wid * C_::B_BPW + x) * (1024 / C_::RB) + lane / C_::CPB;
     const int c = (lane % C_::CPB) ^ swz<C_::RB>(s);
-    int64_t gn = n0 + b_row_of_slot<C_::WN>(s);
-    gn = gn < g.N ? gn : g.N - 1;
     cb[x] = c * 16;
-    pb[x] = static_cast<const uint8_t*>(g.B) + gn * g.ldb + (F6 ? 0 : (int64_t)st0 * C_::RB) + c * 16;
+    ob[x] = (uint32_t)min(b_row_of_slot<C_::WN>(s), n_left - 1) * ldb + c * 16;
+  }
+  // the FP6 gradient loops advance each lane's own addresses: with scalar bases their 8 loads
+  // a stage leave in one burst, and these loops, which LDS traffic bounds, lost 3 to 8 % (dX
+  // 292 -> 303, dW 190 -> 206 us at N = 16384, 4096 x 4096), where the others gained 2 %
+  constexpr bool LANE_ADDR = F6 && F6K != 0;
+  const uint8_t* pa[LANE_ADDR ? C_::A_BPW : 1];
+  const uint8_t* pb[LANE_ADDR ? C_::B_BPW : 1];
+  if constexpr (LANE_ADDR) {
+#pragma unroll
+    for (int x = 0; x < C_::A_BPW; ++x) pa[x] = baseA + oa[x];
+#pragma unroll
+    for (int x = 0; x < C_::B_BPW; ++x) pb[x] = baseB + ob[x];
   }
   // issue the loads of local stage st into buffer st % NBUF; chunks past K are zeroed
   // FP6: the byte offset of global stage gs in the rows (a byte per code, same for A and B),
@@ -406,53 +440,63 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
       const int64_t da = upper ? dA2 : 0;
       if (kin + C_::RA <= K) {
 #pragma unroll
-        for (int x = 0; x < C_::A_BPW; ++x) dma16(pa[x] + da + kin, sa + (wid * C_::A_BPW + x) * 1024);
+        for (int x = 0; x < C_::A_BPW; ++x) {
+          if constexpr (LANE_ADDR) dma16_at(pa[x] + da + kin, sa + (wid * C_::A_BPW + x) * 1024);
+          else dma16(baseA + da + kin, oa[x], sa + (wid * C_::A_BPW + x) * 1024);
+        }
 #pragma unroll
-        for (int x = 0; x < C_::B_BPW; ++x) dma16(pb[x] + kin, sb + (wid * C_::B_BPW + x) * 1024);
+        for (int x = 0; x < C_::B_BPW; ++x) {
+          if constexpr (LANE_ADDR) dma16_at(pb[x] + kin, sb + (wid * C_::B_BPW + x) * 1024);
+          else dma16(baseB + kin, ob[x], sb + (wid * C_::B_BPW + x) * 1024);
+        }
         return;
       }
 #pragma unroll
       for (int x = 0; x < C_::A_BPW; ++x) {
         uint8_t* dst = sa + (wid * C_::A_BPW + x) * 1024;
-        if (kin + ca[x] < K)
-          dma16(pa[x] + da + kin, dst);
-        else
+        if (kin + ca[x] < K) {
+          if constexpr (LANE_ADDR) dma16_at(pa[x] + da + kin, dst);
+          else dma16(baseA + da + kin, oa[x], dst);
+        } else
           *reinterpret_cast<uint4*>(dst + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
       }
 #pragma unroll
       for (int x = 0; x < C_::B_BPW; ++x) {
         uint8_t* dst = sb + (wid * C_::B_BPW + x) * 1024;
-        if (kin + cb[x] < K)
-          dma16(pb[x] + kin, dst);
-        else
+        if (kin + cb[x] < K) {
+          if constexpr (LANE_ADDR) dma16_at(pb[x] + kin, dst);
+          else dma16(baseB + kin, ob[x], dst);
+        } else
           *reinterpret_cast<uint4*>(dst + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
       }
       return;
     }
+    const uint8_t* const sA = baseA + (TRA ? (int64_t)st * C_::KS * g.lda : (int64_t)st * C_::RA);
+    const uint8_t* const sB = baseB + (int64_t)st * C_::RB;
     if constexpr (TRA) {  // whole stages (K a multiple of 128): A advances by 128 rows
 #pragma unroll
       for (int x = 0; x < C_::A_BPW; ++x)
-        dma16(pa[x] + (int64_t)st * C_::KS * g.lda, sa + (wid * C_::A_BPW + x) * 1024);
+        dma16(sA, oa[x], sa + (wid * C_::A_BPW + x) * 1024);
 #pragma unroll
       for (int x = 0; x < C_::B_BPW; ++x)
-        dma16(pb[x] + (int64_t)st * C_::RB, sb + (wid * C_::B_BPW + x) * 1024);
+        dma16(sB, ob[x], sb + (wid * C_::B_BPW + x) * 1024);
       return;
     }
     const int64_t ka = (int64_t)(st0 + st) * C_::RA, kb = (int64_t)(st0 + st) * C_::RB;
     if (ka + C_::RA <= Ka && kb + C_::RB <= Kb) {  // whole stage inside K: straight line
 #pragma unroll
       for (int x = 0; x < C_::A_BPW; ++x)
-        dma16(pa[x] + (int64_t)st * C_::RA, sa + (wid * C_::A_BPW + x) * 1024);
+        dma16(sA, oa[x], sa + (wid * C_::A_BPW + x) * 1024);
 #pragma unroll
       for (int x = 0; x < C_::B_BPW; ++x)
-        dma16(pb[x] + (int64_t)st * C_::RB, sb + (wid * C_::B_BPW + x) * 1024);
+        dma16(sB, ob[x], sb + (wid * C_::B_BPW + x) * 1024);
       return;
     }
 #pragma unroll
     for (int x = 0; x < C_::A_BPW; ++x) {
       uint8_t* dst = sa + (wid * C_::A_BPW + x) * 1024;
       if (ka + ca[x] < Ka)
-        dma16(pa[x] + (int64_t)st * C_::RA, dst);
+        dma16(sA, oa[x], dst);
       else
         *reinterpret_cast<uint4*>(dst + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
     }
@@ -460,11 +504,20 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
     for (int x = 0; x < C_::B_BPW; ++x) {
       uint8_t* dst = sb + (wid * C_::B_BPW + x) * 1024;
       if (kb + cb[x] < Kb)
-        dma16(pb[x] + (int64_t)st * C_::RB, dst);
+        dma16(sB, ob[x], dst);
       else
         *reinterpret_cast<uint4*>(dst + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
     }
   };
+
+  // the first stages' loads go out before everything that does not need them: the scale, the
+  // accumulators and the fragment addresses
+  if constexpr (!LANE_ADDR) {
+#pragma unroll
+    for (int p = 0; p < C_::NBUF - 1; ++p)
+      if (p < nst) issue(p);
+    read_scale();
+  }
 
   // int32 accumulators; the FP6 route accumulates in fp32 (accf, exact integers) and its
   // epilogues read those directly (the gradient ones convert a row block at a time)
@@ -583,7 +636,7 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
       int64_t col = n0 + (int64_t)(lane & 3) * 64;  // one 128-byte line of fp16
       col = col < g.N ? col : n0;
 #pragma unroll
-      for (int x = 0; x < 2; ++x) dma16(g.delta + (int64_t)pf_row[x] * g.ldo + col, pf_sink);
+      for (int x = 0; x < 2; ++x) dma16_at(g.delta + (int64_t)pf_row[x] * g.ldo + col, pf_sink);
     }
   };
   auto stage_ready = [&](int st) {  // this wave's loads of stage st landed, then all waves'
@@ -711,9 +764,11 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
         if (d > 0) scale_all(d);
       }
     };
+    if constexpr (LANE_ADDR) {
 #pragma unroll
-    for (int p = 0; p < C_::NBUF - 1; ++p)
-      if (p < nst) issue(p);
+      for (int p = 0; p < C_::NBUF - 1; ++p)
+        if (p < nst) issue(p);
+    }
     if constexpr (KST == 1) {
       if (nst > 0) {
         stage_ready(0);
@@ -773,9 +828,6 @@ __global__ __launch_bounds__((Cfg<BM, A4, WN, BN_, F6>::THREADS), (Cfg<BM, A4, W
       }
     }
   } else {
-  #pragma unroll
-    for (int p = 0; p < C_::NBUF - 1; ++p)
-      if (p < nst) issue(p);
     if (nst > 0) {
       stage_ready(0);
       read_pair(0, 0, 0);
