@@ -183,7 +183,7 @@ int gemm_split_override();                          // the test hook's forced fa
 // padded FP6 layout [rows][K]: every 32 codes become 24 bytes of e2m3 fields (field i at
 // bits 6i..6i+5, little-endian) followed by 8 zero bytes.  K a multiple of 64.
 hipError_t launch_int4_to_fp6(hipStream_t s, const uint8_t* src, uint8_t* dst, int64_t rows, int64_t K);
-// Row orders of the FP6 backward from the sample's weights (one workgroup, N <= 65536):
+// Row orders of the FP6 backward from the sample's weights (N <= 65536; w_up, w_dn 16-byte aligned):
 // order6[n_kept] (upper tokens first), *n_up, the dW entries ent[] grouped by weight class
 // (capacity 4 N + 640, -1 = padding) and cls[5] = first entries of classes 3, 2, 1, 0 and
 // the padded entry count.

@@ -536,7 +536,7 @@ __global__ __launch_bounds__(256) void build_operands_kernel(
   }
 }
 
-// Orders of the kept rows for the FP6 MFMA route (gemm6.hip), one workgroup per problem.
+// Orders of the kept rows for the FP6 MFMA route (gemm6.hip), one workgroup per 1024 tokens.
 // Categories of a token t: upper (w_up = 1), kept lower-only (w_up = 0, w_dn > 0), and the
 // lower weight class e = log2 w_dn (0..4).
 //   order6: the kept tokens, upper tokens first, each part ascending (the dX row order:
@@ -546,44 +546,81 @@ __global__ __launch_bounds__(256) void build_operands_kernel(
 //           GEMM stage).  The upper weight 14 = 8 + 4 + 2 puts each upper row into classes
 //           3, 2 and 1 (after that class's lower rows);
 //   cls:    the first entries of classes 3, 2, 1, 0 and the padded total.
-// Each thread owns a contiguous range of tokens, so a block-wide exclusive scan of the
-// per-thread counts places every token in ascending order within its category.
+// Every workgroup counts the categories over all tokens and over those before its own, from
+// the weight bytes (16 tokens a thread, by popcounts; 32 KB for N = 16384, read from L2), and
+// so knows its places without waiting for another; its own tokens, one per thread, are ranked
+// by ballots.  One workgroup for all tokens: 36.4 us at N = 16384, 5.6 us so.
 constexpr int kCat = 7;  // upper, lower-only, lower classes 0..4
 __global__ __launch_bounds__(1024) void fp6_plan_kernel(
     const uint8_t* __restrict__ w_up, const uint8_t* __restrict__ w_dn, int N,
     int32_t* __restrict__ order6, int32_t* __restrict__ n_up_out, int32_t* __restrict__ ent,
     int32_t* __restrict__ cls) {
-  __shared__ int s_cnt[kCat][1024];
-  __shared__ int s_tot[kCat];
+  __shared__ uint32_t s_sum[16][8];  // per wave: categories in pairs of halves, all tokens then before
+  __shared__ int s_tot[8], s_bef[8];
+  __shared__ int s_wave[16][kCat];   // kept tokens of each wave, then those of the waves before
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int per = (N + 1023) / 1024;
-  const int t0 = tid * per, t1 = min(N, t0 + per);
-  int c[kCat];
+  const int T0 = (int)blockIdx.x * 1024, t = T0 + tid;
+  const int up = t < N ? w_up[t] : 0, dn = t < N ? w_dn[t] : 0;
+  uint32_t sum[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+  for (int q = 16 * tid; q < N; q += 16 * 1024) {  // at most 64 tokens a thread: halves of a wave sum fit
+    uint32_t u[4] = {0u, 0u, 0u, 0u}, d[4] = {0u, 0u, 0u, 0u};
+    if (q + 16 <= N) {
+      const uint4 a = *reinterpret_cast<const uint4*>(w_up + q), b = *reinterpret_cast<const uint4*>(w_dn + q);
+      u[0] = a.x; u[1] = a.y; u[2] = a.z; u[3] = a.w;
+      d[0] = b.x; d[1] = b.y; d[2] = b.z; d[3] = b.w;
+    } else {
 #pragma unroll
-  for (int k = 0; k < kCat; ++k) c[k] = 0;
-  for (int t = t0; t < t1; ++t) {
-    const int up = w_up[t], dn = w_dn[t];
-    if (up) ++c[0];
-    else if (dn) ++c[1];
-    if (dn) ++c[2 + (31 - __clz(dn))];
+      for (int j = 0; j < 16; ++j)
+        if (q + j < N) {
+          u[j >> 2] |= (uint32_t)w_up[q + j] << (8 * (j & 3));
+          d[j >> 2] |= (uint32_t)w_dn[q + j] << (8 * (j & 3));
+        }
+    }
+    constexpr uint32_t kOnes = 0x01010101u;
+    uint32_t c[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t any = (d[w] | (d[w] >> 1) | (d[w] >> 2) | (d[w] >> 3) | (d[w] >> 4)) & kOnes;
+      c[0] += __builtin_popcount(u[w] & kOnes) | (__builtin_popcount(any & ~u[w]) << 16);
+      c[1] += __builtin_popcount(d[w] & kOnes) | (__builtin_popcount((d[w] >> 1) & kOnes) << 16);
+      c[2] += __builtin_popcount((d[w] >> 2) & kOnes) | (__builtin_popcount((d[w] >> 3) & kOnes) << 16);
+      c[3] += __builtin_popcount((d[w] >> 4) & kOnes);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      sum[i] += c[i];
+      if (q < T0) sum[4 + i] += c[i];
+    }
   }
 #pragma unroll
-  for (int k = 0; k < kCat; ++k) s_cnt[k][tid] = c[k];
+  for (int i = 0; i < 8; ++i) {
+    sum[i] = wave_sum_u32_dpp(sum[i]);
+    if (lane == 0) s_sum[wv][i] = sum[i];
+  }
+  // this thread's token: its category's rank among the wave's
+  const int e = dn ? 31 - __clz(dn) : -1;
+  int rank_ord = 0, rank_cls = 0;
+#pragma unroll
+  for (int k = 0; k < kCat; ++k) {
+    const bool in = k == 0 ? up != 0 : k == 1 ? (!up && dn) : e == k - 2;
+    const uint64_t b = __ballot(in);
+    const int r = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+    if (in) (k < 2 ? rank_ord : rank_cls) = r;
+    if (lane == 0) s_wave[wv][k] = (int)__builtin_popcountll(b);
+  }
   __syncthreads();
-  if (wv < kCat) {  // wave k: exclusive scan of category k over the 1024 threads
-    int v[16], sum = 0;
+  if (tid < 8 && tid < kCat) {  // category tid: word tid / 2, half tid % 2
+    int all = 0, before = 0, run = 0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { v[i] = s_cnt[wv][16 * lane + i]; sum += v[i]; }
-    int incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(incl, o);
-      if (lane >= o) incl += y;
+    for (int w = 0; w < 16; ++w) {
+      all += (int)((s_sum[w][tid >> 1] >> (16 * (tid & 1))) & 0xFFFFu);
+      before += (int)((s_sum[w][4 + (tid >> 1)] >> (16 * (tid & 1))) & 0xFFFFu);
+      const int n = s_wave[w][tid];
+      s_wave[w][tid] = run;
+      run += n;
     }
-    int run = incl - sum;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) { s_cnt[wv][16 * lane + i] = run; run += v[i]; }
-    if (lane == 63) s_tot[wv] = incl;
+    s_tot[tid] = all;
+    s_bef[tid] = before;
   }
   __syncthreads();
   const int n_up = s_tot[0], n_d0 = s_tot[2], n_d1 = s_tot[3], n_d2 = s_tot[4], n_d3 = s_tot[5],
@@ -592,26 +629,17 @@ __global__ __launch_bounds__(1024) void fp6_plan_kernel(
   const int b3 = r128(n_d4), b2 = b3 + r128(n_d3 + n_up), b1 = b2 + r128(n_d2 + n_up),
             b0 = b1 + r128(n_d1 + n_up), ke = b0 + r128(n_d0);
   const int base[5] = {b0, b1, b2, b3, 0};  // first entry of lower class e
-  int p_up = s_cnt[0][tid], p_rest = n_up + s_cnt[1][tid];
-  int p_d[5];
-#pragma unroll
-  for (int e = 0; e < 5; ++e) p_d[e] = base[e] + s_cnt[2 + e][tid];
-  for (int t = t0; t < t1; ++t) {
-    const int up = w_up[t], dn = w_dn[t];
-    if (up) {
-      order6[p_up] = t;
-      ent[b3 + n_d3 + p_up] = 2 * t + 1;
-      ent[b2 + n_d2 + p_up] = 2 * t + 1;
-      ent[b1 + n_d1 + p_up] = 2 * t + 1;
-      ++p_up;
-    } else if (dn) {
-      order6[p_rest++] = t;
-    }
-    if (dn) {
-      const int e = 31 - __clz(dn);
-      ent[p_d[e]++] = 2 * t;
-    }
+  if (up) {
+    const int p = s_bef[0] + s_wave[wv][0] + rank_ord;
+    order6[p] = t;
+    ent[b3 + n_d3 + p] = 2 * t + 1;
+    ent[b2 + n_d2 + p] = 2 * t + 1;
+    ent[b1 + n_d1 + p] = 2 * t + 1;
+  } else if (dn) {
+    order6[n_up + s_bef[1] + s_wave[wv][1] + rank_ord] = t;
   }
+  if (dn) ent[base[e] + s_bef[2 + e] + s_wave[wv][2 + e] + rank_cls] = 2 * t;
+  if (blockIdx.x) return;
   // padding of every class to its 128-entry boundary
   const int pad_lo[5] = {n_d4, b3 + n_d3 + n_up, b2 + n_d2 + n_up, b1 + n_d1 + n_up, b0 + n_d0};
   const int pad_hi[5] = {b3, b2, b1, b0, ke};
@@ -672,7 +700,7 @@ hipError_t launch_build_operands(hipStream_t s, int dt, const uint8_t* qup, cons
 hipError_t launch_fp6_plan(hipStream_t s, const uint8_t* w_up, const uint8_t* w_dn, int64_t N,
                            int32_t* order6, int32_t* n_up, int32_t* ent, int32_t* cls) {
   timing_begin(s);
-  fp6_plan_kernel<<<1, 1024, 0, s>>>(w_up, w_dn, (int)N, order6, n_up, ent, cls);
+  fp6_plan_kernel<<<(unsigned)((N + 1023) / 1024), 1024, 0, s>>>(w_up, w_dn, (int)N, order6, n_up, ent, cls);
   timing_end(s, kKFp6Plan);
   return hipGetLastError();
 }
