@@ -202,13 +202,17 @@ int grad_bn(int64_t M, int64_t N, int splits) {
 }
 
 // Tile width of a forward (INT4 x INT4) GEMM by the same rule, the tiles of all batches
-// counted; its 128-wide tiles use 64 x 64 wave tiles.
-int fwd_bn(int64_t M, int64_t N, int splits, int64_t batch) {
+// counted; its 128-wide tiles use 64 x 64 wave tiles.  They also take products of up to 16
+// stages whose 256-wide tiles would leave half of a second round empty (kernel times, 256 and
+// 128 wide: 640 tiles, 10240 x 1024 -> 2048, 28.4 and 23.9 us, 768, 8192 x 1024 -> 3072, 28.9
+// and 27.0; longer products and further rounds lose: 688 tiles, 11000 x 8192 -> 2048, 151 and
+// 162 us, 1280, 10240 x 2048 -> 4096, 73.6 and 79.4 us).
+int fwd_bn(int64_t M, int64_t N, int64_t K, int splits, int64_t batch) {
   if (splits > 1) return kBN;
   if (g_bn_override) return g_bn_override;
   const int64_t bm = tile_m<true>();
   const int64_t t256 = ((M + bm - 1) / bm) * ((N + kBN - 1) / kBN) * (batch > 0 ? batch : 1);
-  return 4 * t256 <= 3 * 512 ? kMidBN : kBN;
+  return 4 * t256 <= 3 * 512 || (t256 > 512 && t256 <= 768 && K <= 16 * kKS) ? kMidBN : kBN;
 }
 
 // the Hadamard block is a template parameter of the gradient epilogues
@@ -253,7 +257,7 @@ hipError_t gemm_b(hipStream_t s, const GemmArgs& g, int splits, int id) {
     }
     return hipErrorInvalidValue;
   } else {
-    if (fwd_bn(g.M, g.N, splits, g.batch) == kMidBN) return gemm_t<BM, A4, EPI, DT, 0, kMidBN, false, 0, TRA>(s, g, splits, id);
+    if (fwd_bn(g.M, g.N, g.K, splits, g.batch) == kMidBN) return gemm_t<BM, A4, EPI, DT, 0, kMidBN, false, 0, TRA>(s, g, splits, id);
     return gemm_t<BM, A4, EPI, DT, 0, kBN, false, 0, TRA>(s, g, splits, id);
   }
 }
@@ -293,8 +297,6 @@ hipError_t run_dt(hipStream_t s, int dt, const GemmArgs& g, int splits, int32_t*
 
 }  // namespace
 
-int gemm_fwd_bn(int64_t M, int64_t N, int splits, int64_t batch) { return fwd_bn(M, N, splits, batch); }
-int gemm_grad_bn(int64_t M, int64_t N, int splits) { return grad_bn(M, N, splits); }
 
 hipError_t launch_gemm_reduce(hipStream_t s, int epi, int dt, const int32_t* P, int S, const GemmArgs& g) {
   switch (epi) {

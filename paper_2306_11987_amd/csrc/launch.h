@@ -169,10 +169,8 @@ hipError_t launch_gemm(hipStream_t s, int epi, int dt, bool a_int4, bool b_int4,
 bool gemm_small(int64_t M, int64_t N, int splits, int64_t batch);
 hipError_t launch_gemm_small(hipStream_t s, int epi, int dt, bool a_int4, const GemmArgs& g);
 int gemm_small_bn(int log2b);  // tile width of its gradient products
-// Tile widths the launchers choose (forward, gradients), and the split-K reduction with the
-// epilogue of `epi` on its own (kEpiAcc, kEpiFwd, kEpiDx, kEpiDw).
-int gemm_fwd_bn(int64_t M, int64_t N, int splits, int64_t batch);
-int gemm_grad_bn(int64_t M, int64_t N, int splits);
+// The split-K reduction with the epilogue of `epi` on its own (kEpiAcc, kEpiFwd, kEpiDx,
+// kEpiDw).
 hipError_t launch_gemm_reduce(hipStream_t s, int epi, int dt, const int32_t* P, int S, const GemmArgs& g);
 // The same products on the FP6 MFMA: both operands in the padded FP6 layout of
 // launch_int4_to_fp6 (lda, ldb = K bytes), results identical to launch_gemm's.
