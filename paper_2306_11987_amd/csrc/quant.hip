@@ -40,6 +40,7 @@
 #include "launch.h"
 
 #include <mutex>
+#include <type_traits>
 #include <unordered_map>
 
 namespace hqlss {
@@ -114,6 +115,34 @@ __device__ __forceinline__ void fwht16(float v[16], int lane) {
   HQLSS_XSTAGE(2)
   HQLSS_XSTAGE(4)
 #undef HQLSS_XSTAGE
+}
+
+// The same with 32 consecutive elements in a lane.
+template <int LOG2B>
+__device__ __forceinline__ void fwht32(float v[32], int lane) {
+  constexpr int b = 1 << LOG2B;
+#pragma unroll
+  for (int h = 1; h < 32 && h < b; h <<= 1) {
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+      if ((j & h) == 0) {
+        const float a = v[j], c = v[j + h];
+        v[j] = a + c;
+        v[j + h] = a - c;
+      }
+    }
+  }
+#define HQLSS_XSTAGE32(M)                                                     \
+  if constexpr (32 * (M) < b) {                                               \
+    const uint32_t sgn = (lane & (M)) ? 0x80000000u : 0u;                     \
+    _Pragma("unroll") for (int j = 0; j < 32; ++j) {                          \
+      const float own = __uint_as_float(__float_as_uint(v[j]) ^ sgn);         \
+      v[j] = add_xor_lane<M>(v[j], own);                                      \
+    }                                                                         \
+  }
+  HQLSS_XSTAGE32(1)
+  HQLSS_XSTAGE32(2)
+#undef HQLSS_XSTAGE32
 }
 
 // Bits of fl(x + 1.5 * 2^23): rint(x) (half-to-even) sits in the low mantissa bits.
@@ -247,6 +276,39 @@ struct Geo {
   }
 };
 
+// The row groups of Geo with 32 elements a lane and half the lanes a row: the second half of
+// the workgroup's threads takes the rows of the next round, so that a row stays on the
+// workgroup (and XCD) that Geo gives it.
+struct Geo32 {
+  int lane, sub, G, iters, chunks, spare;
+  int64_t first_row, row_step, rows, steps;
+  __device__ Geo32(const QJob& j, int wg) {
+    const int l = j.log2g - 1;  // lanes per row; log2g >= 2, and >= 3 where a block has 128 columns
+    lane = threadIdx.x & 63;
+    G = 1 << l;
+    sub = threadIdx.x & (G - 1);
+    chunks = (int)(j.cols / 32);
+    iters = (chunks + G - 1) >> l;
+    spare = chunks % 4 == 0 ? 3 : 1;  // whole blocks, as spare_mask()
+    const int rw = kQThreads >> j.log2g;  // Geo's rows of a workgroup at a time
+    const int64_t round = (int64_t)j.wg * rw;
+    auto row = [&](int t) { return (int64_t)wg * rw + (t >> l) % rw + (t >> l) / rw * round; };
+    first_row = row(threadIdx.x);
+    row_step = 2 * round;
+    rows = j.rows;
+    const int64_t row0 = row(threadIdx.x & ~63u);  // the wave's first
+    steps = row0 < rows ? (rows - row0 + row_step - 1) / row_step * iters : 0;
+  }
+  __device__ int64_t row_of(int64_t k) const {
+    const int64_t r = first_row + k * row_step;
+    return r < rows ? r : rows - 1;
+  }
+  __device__ int load_col(int it) const {
+    const int c = it * G + sub;
+    return (c < chunks ? c : (sub & spare)) * 32;
+  }
+};
+
 // Geometry of the block-size search, which has no per-row results: the tensor is one run of
 // 16-element chunks, 64 to a wave and step, whatever its rows: a row is a multiple of 64
 // elements and of the Hadamard block, so blocks never straddle a row and stay aligned.
@@ -317,16 +379,35 @@ __global__ __launch_bounds__(kQThreads) void fwht_absmax_kernel(QJob j0, QJob j1
   // steps in flight: 2 measured faster than 4 (fewer registers, more waves per SIMD;
   // -5 % per FFN step's maximum passes, -9 % on the 4096..11008-wide sweep) and than 8
   constexpr int U = 2;
+  // blocks of 32 columns and more: the two steps are one of 32 elements in a row, one lane
+  // exchange less an element (at b = 128 the one that goes through LDS); vector instructions
+  // bound this pass there (16384 x 4096 and 4096 x 4096 bf16, b = 128: 42.5 -> 40.3 us;
+  // 16384 x 768 and 3072 x 768 fp16, b = 32: 8.4 -> 7.6).  Not for fp32, whose lanes would
+  // load 128 bytes each (1003 x 832: 4.6 -> 5.2)
+  constexpr bool WIDE = LOG2B >= 5 && DT != kF32;
   __shared__ float red[kQWaves];
   const QPos q = qpos(j0, j1);
   const QJob& j = q.second ? j1 : j0;
   const int wg = q.wg;
-  const Geo g(j, wg);
+  using G_ = std::conditional_t<WIDE, Geo32, Geo>;
+  const G_ g(j, wg);
   constexpr int EB = Elem<DT>::bytes;
   float m = 0.f;
   const char* base = static_cast<const char*>(j.src) + (int64_t)q.b * j.bstride * EB;
   int64_t k = 0;
   int it = 0;
+  if constexpr (WIDE) {
+    for (int64_t s0 = 0; s0 < g.steps; ++s0) {
+      float v[32];
+      const char* p = base + (g.row_of(k) * j.cols + g.load_col(it)) * EB;
+      load16<DT, HQ_NT_ABS_LD>(p, v);
+      load16<DT, HQ_NT_ABS_LD>(p + 16 * EB, v + 16);
+      if (++it == g.iters) { it = 0; ++k; }
+      fwht32<LOG2B>(v, g.lane);  // rows and chunks loaded twice leave the maximum unchanged
+#pragma unroll
+      for (int e = 0; e < 32; e += 2) m = fmaxf(m, fmaxf(fabsf(v[e]), fabsf(v[e + 1])));
+    }
+  } else
   for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
     float v[U][kVE];
 #pragma unroll
@@ -472,8 +553,8 @@ __global__ __launch_bounds__(kQThreads) void fwht_quant_kernel(QJob j0, QJob j1,
   int64_t k = 0, kp = 0;  // load and process positions
   int it = 0, ip = 0;
   int ss = 0;
-  Raw16<DT> raw[U];
-  auto load = [&](int64_t s0) {
+  Raw16<DT> raw[U], next[U];
+  auto load = [&](Raw16<DT>* raw, int64_t s0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
@@ -482,12 +563,12 @@ __global__ __launch_bounds__(kQThreads) void fwht_quant_kernel(QJob j0, QJob j1,
       }
     }
   };
-  load(0);  // in flight while the maximum is formed
+  load(raw, 0);  // in flight while the maximum is formed
   const float a = reduce_parts(o.part, o.nparts);
   if (wg == 0 && threadIdx.x == 0) *o.amax_out = a;
   const float inv = a > 0.f ? 7.0f / a : 0.f;
   for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
-    if (s0) load(s0);
+    load(next, s0 + U);  // the next steps' loads, in flight while these are quantised
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
@@ -519,6 +600,8 @@ __global__ __launch_bounds__(kQThreads) void fwht_quant_kernel(QJob j0, QJob j1,
         }
       }
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) raw[u] = next[u];
   }
 }
 
