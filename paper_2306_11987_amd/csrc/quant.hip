@@ -1150,7 +1150,7 @@ void choose_group(QJob& j) {
   };
   int best = j.log2g;
   for (int l = j.log2g + 1; (1 << l) <= kQThreads && (chunks >> (l - 1)) > 0; ++l)
-    if (steps(l) < steps(best)) best = l;
+    if (steps(l) < steps(best) || (best != j.log2g && l <= 6 && steps(l) == steps(best))) best = l;
   j.log2g = best;
 }
 
