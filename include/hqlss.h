@@ -384,6 +384,14 @@ void hqlss_debug_set_fwd_fp6(int mode);
  * 0 and sets *pitch to 0 for N < 1. */
 size_t hqlss_debug_plan_scores_offset(int64_t N, int64_t *pitch);
 
+/* Test hook (host only): how the row kernels share a resident grid of `cap` workgroups (a
+ * multiple of 256, at most 1024) between two tensors rows0 x cols and rows1 x cols (rows1 = 0:
+ * one tensor), `batch` of each: out[0], out[1] workgroups (per batch), out[2], out[3] log2 of
+ * the lanes of a row.  flat != 0: the block-size search's kernels, which take no row groups.
+ * Errors: HQLSS_ERR_NULL, HQLSS_ERR_SHAPE, HQLSS_ERR_ARG (cap). */
+hqlss_status hqlss_debug_row_grid(int64_t rows0, int64_t rows1, int64_t cols, int64_t batch,
+                                  int cap, int flat, int *out);
+
 /* Benchmark hook: a plain device-to-device copy kernel ("copy") of `bytes` bytes (a
  * multiple of 16, both pointers 16-byte aligned, non-overlapping), asynchronous on
  * `stream`.  Its bytes read and written are known exactly, which calibrates hardware

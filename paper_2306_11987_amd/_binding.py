@@ -84,6 +84,7 @@ def _load() -> ctypes.CDLL:
         "hqlss_debug_set_gemm_splits": (None, [_int]),
         "hqlss_debug_set_gemm_tile_n": (None, [_int]),
         "hqlss_debug_set_fwd_fp6": (None, [_int]),
+        "hqlss_debug_row_grid": (st, [_i64, _i64, _i64, _i64, _int, _int, ctypes.POINTER(ctypes.c_int)]),
         "hqlss_debug_copy": (st, [_vp, _vp, _sz, _vp]),
         "hqlss_debug_plan_scores_offset": (_sz, [_i64, ctypes.POINTER(_i64)]),
     }
@@ -478,6 +479,13 @@ def debug_plan_scores_offset(N: int):
     pitch = ctypes.c_int64(0)
     off = lib.hqlss_debug_plan_scores_offset(int(N), ctypes.byref(pitch))
     return int(off), int(pitch.value)
+
+
+def debug_row_grid(rows0: int, rows1: int, cols: int, batch: int = 1, cap: int = 1024, flat: bool = False):
+    """Test hook (host only): (workgroups, log2 lanes a row) of each of two tensors sharing a grid."""
+    out = (ctypes.c_int * 4)()
+    _check(lib.hqlss_debug_row_grid(rows0, rows1, cols, batch, cap, int(flat), out), "hqlss_debug_row_grid")
+    return (out[0], out[2]), (out[1], out[3])
 
 
 def debug_copy(src: torch.Tensor, dst: torch.Tensor) -> None:

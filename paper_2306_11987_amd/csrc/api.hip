@@ -1129,6 +1129,18 @@ size_t hqlss_debug_plan_scores_offset(int64_t N, int64_t* pitch) {
   return plan_scores_offset();
 }
 
+hqlss_status hqlss_debug_row_grid(int64_t rows0, int64_t rows1, int64_t cols, int64_t batch,
+                                  int cap, int flat, int* out) {
+  if (!out) return HQLSS_ERR_NULL;
+  if (rows0 < 1 || rows1 < 0 || batch < 1 || cols < 64 || cols % 64) return HQLSS_ERR_SHAPE;
+  if (cap < 256 || cap > kQMaxWg || cap % 256) return HQLSS_ERR_ARG;
+  QJob j0 = make_job_batched(nullptr, batch, rows0, cols);
+  QJob j1 = rows1 ? make_job_batched(nullptr, batch, rows1, cols) : make_job(nullptr, 0, cols);
+  row_grid(j0, j1, cap, flat != 0);
+  out[0] = j0.wg; out[1] = j1.wg; out[2] = j0.log2g; out[3] = j1.log2g;
+  return HQLSS_OK;
+}
+
 hqlss_status hqlss_debug_copy(const void* src, void* dst, size_t bytes, void* stream) {
   if (!src || !dst) return HQLSS_ERR_NULL;
   if (!a16(src) || !a16(dst)) return HQLSS_ERR_ALIGN;

@@ -95,6 +95,9 @@ hipError_t launch_bit_split(hipStream_t s, int dt, QJob& j, const float* part, i
 hipError_t launch_hsize_search(hipStream_t s, int dt, QJob& j0, QJob& j1, float* mx0, float* mx1,
                                double* err0, double* err1, int kmax, int32_t* k_out,
                                double* mse_out);
+// The row groups and workgroups the row kernels would take for two jobs (flat: the block-size
+// search's) on a grid of `cap` resident workgroups; stored into the jobs.  Host only.
+void row_grid(QJob& j0, QJob& j1, int cap, bool flat);
 // leverage scores, clamp-rescale, masks, compaction (one workgroup per batch; batch b reads
 // and writes its own blocks: N rows, 2 score_pitch scores, nparts partials, one n_kept, and
 // draws at counter offset + b offset_stride).

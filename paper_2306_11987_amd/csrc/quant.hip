@@ -1166,7 +1166,7 @@ int64_t wgs_needed(const QJob& j, bool flat) {
 }
 
 // Share one resident grid between two jobs: all they need if it fits, else in proportion
-// to their sizes (each at least one workgroup).
+// to their sizes.
 // flat: a kernel that takes the tensors as runs of chunks; else the row groups are chosen here.
 void fit_grid(QJob& a, QJob& b, int cap, bool flat = false) {
   if (!flat) {
@@ -1195,13 +1195,21 @@ void fit_grid(QJob& a, QJob& b, int cap, bool flat = false) {
     b.wg = nb ? per(cb, nb, b.batch) : 0;
     return;
   }
+  // Whole rounds of the 8 XCDs: job 1's share is rounded up where that leaves job 0 at least
+  // 7/8 of its own share, else down; each job with rows gets at least 8.  (Rounded up always, a
+  // short batch beside a wide weight was left one workgroup of the grid: 64 x 4096 and 11008 x
+  // 4096 fp16, maximum 36.5 us, block search 146.)
   const double ba = (double)a.rows * a.cols, bb = (double)b.rows * b.cols;
-  int64_t wb = nb ? (int64_t)(cap * bb / (ba + bb) + 0.5) : 0;
-  wb = (wb + 7) / 8 * 8;  // whole rounds of the 8 XCDs
-  if (nb && wb < 1) wb = 1;
-  if (wb > nb) wb = nb;
+  int64_t wb = 0;
+  if (nb) {
+    wb = (int64_t)(cap * bb / (ba + bb) + 0.5);
+    const int64_t up = (wb + 7) / 8 * 8;
+    wb = 8 * (cap - up) >= 7 * (cap - wb) ? up : wb / 8 * 8;
+    if (na && wb > cap - 8) wb = cap - 8;
+    if (wb < 8) wb = 8;
+    if (wb > nb) wb = nb;
+  }
   int64_t wa = cap - wb;
-  if (na && wa < 1) wa = 1;
   if (wa > na) wa = na;
   a.wg = (int)wa;
   b.wg = (int)wb;
@@ -1342,6 +1350,8 @@ hipError_t launch_bit_split(hipStream_t s, int dt, QJob& j, const float* part, i
   return hipGetLastError();
 }
 
+
+void row_grid(QJob& j0, QJob& j1, int cap, bool flat) { fit_grid(j0, j1, cap, flat); }
 
 hipError_t launch_hsize_search(hipStream_t s, int dt, QJob& j0, QJob& j1, float* mx0, float* mx1,
                                double* err0, double* err1, int kmax, int32_t* k_out,

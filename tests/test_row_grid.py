@@ -1,0 +1,37 @@
+"""How the row kernels share a grid between two tensors and choose their row groups (host logic)."""
+import pytest
+
+H = pytest.importorskip("paper_2306_11987_amd", reason="libhqlss.so not built")
+
+WG = 512  # threads of a workgroup
+
+
+def needed(rows, cols, log2g, flat):
+    if flat:
+        return -(-rows * (cols // 16) // WG)
+    return -(-rows // (WG >> log2g))
+
+
+@pytest.mark.parametrize("flat", [False, True])
+@pytest.mark.parametrize("cap", [512, 768, 1024])
+def test_no_job_loses_its_share_of_the_grid(cap, flat):
+    """The grid fits the device, and each job gets what it needs or at least 7/8 of its share by
+    size, rounded down to 8 workgroups: a short batch beside a wide weight once got a single one."""
+    rows = [1, 7, 16, 33, 48, 64, 80, 127, 200, 777, 1024, 5001, 16384, 65536]
+    for cols in (64, 832, 1024, 4096, 8192, 11008):
+        for r0 in rows:
+            for r1 in rows[4:]:
+                jobs = H.debug_row_grid(r0, r1, cols, cap=cap, flat=flat)
+                wg = [j[0] for j in jobs]
+                assert min(wg) >= 1 and sum(wg) <= cap, (cols, r0, r1, wg)
+                for r, (w, l) in zip((r0, r1), jobs):
+                    share = cap * r // (r0 + r1)
+                    want = min(needed(r, cols, l, flat), max(1, 7 * share // 8 // 8 * 8))
+                    assert w >= want, (cols, r0, r1, wg, want)
+
+
+def test_one_tensor_takes_the_whole_grid():
+    for cols in (64, 832, 4096):
+        for r in (1, 100, 16384, 65536):
+            (w, l), (w1, _) = H.debug_row_grid(r, 0, cols)
+            assert w == min(needed(r, cols, l, False), 1024) and w1 == 0
