@@ -188,18 +188,15 @@ __global__ __launch_bounds__(THREADS) void lss_plan_kernel(
   uint64_t S_all = 0, S = 0;
   int64_t k = 0;
   uint64_t rT = 1, rF = 0;  // ceil(S / R) and floor(S / R)
+  // Both are formed before either is assigned, once each and by selection: assigned in three
+  // branches, through the captured references, the state lived in private memory.
   auto set_round = [&]() {
     const int64_t R = B - k;
-    if (S == 0) {
-      rT = 1;
-      rF = 0;
-    } else if (R > 0) {
-      uint64_t rem;
-      rF = quotient(S, (uint32_t)R, rem);
-      rT = rF + (rem ? 1 : 0);
-    } else {
-      rT = rF = ~uint64_t(0);
-    }
+    uint64_t rem;
+    const uint64_t F = quotient(S, R > 0 ? (uint32_t)R : 1u, rem), T = F + (rem ? 1 : 0);
+    const bool none = R <= 0;
+    rT = S == 0 ? 1 : none ? ~uint64_t(0) : T;
+    rF = S == 0 ? 0 : none ? ~uint64_t(0) : F;
   };
   if (wid == 0) {  // totals of the bit-split workgroups: non-zero rows and the score sum
     uint32_t nz = 0;
