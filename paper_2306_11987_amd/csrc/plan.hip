@@ -201,11 +201,18 @@ __global__ __launch_bounds__(THREADS) void lss_plan_kernel(
   if (wid == 0) {  // totals of the bit-split workgroups: non-zero rows and the score sum
     uint32_t nz = 0;
     uint64_t st = 0;
-#pragma unroll 8
-    for (int i = lane; i < nparts; i += 64) {
-      const uint4 p = parts[i];
-      nz += p.x;
-      st += ((uint64_t)p.z << 32) | p.y;
+    // four loads in flight (one after the other, as the remainder of an unrolled loop, 256
+    // partials took 1 us more)
+    for (int i = lane; i < nparts; i += 4 * 64) {
+      uint4 p[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) p[q] = parts[i + 64 * q < nparts ? i + 64 * q : i];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool in = i + 64 * q < nparts;
+        nz += in ? p[q].x : 0u;
+        st += in ? ((uint64_t)p[q].z << 32) | p[q].y : 0ull;
+      }
     }
     nz = wave_sum_u32_dpp(nz);
     S = S_all = wave_sum_u64_dpp(st);
