@@ -741,6 +741,9 @@ __global__ __launch_bounds__(kQThreads) void bit_split_kernel(QJob j, const floa
   int64_t k = 0, kp = 0;
   int it = 0, ip = 0;
   int su = 0, sd = 0;
+  // The first loads go out before the maximum is formed; not for fp32, whose 16 registers of
+  // raw data then cost a third of the workgroups a CU holds (85 registers, with 71 three).
+  constexpr bool EARLY = DT != kF32;
   Raw16<DT> raw[U];
   auto load = [&](int64_t s0) {
 #pragma unroll
@@ -751,12 +754,12 @@ __global__ __launch_bounds__(kQThreads) void bit_split_kernel(QJob j, const floa
       }
     }
   };
-  load(0);  // in flight while the maximum is formed
+  if constexpr (EARLY) load(0);
   const float a = reduce_parts(part + (int64_t)b * nparts, nparts);
   if (wg == 0 && threadIdx.x == 0) o.amax_out[b] = a;
   const float inv = a > 0.f ? 7.0f / a : 0.f;
   for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
-    if (s0) load(s0);
+    if (!EARLY || s0) load(s0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {

@@ -68,3 +68,9 @@ def test_sampler_state_stays_in_registers(resources):
     store and a load into every round of it."""
     for sym, _, private in kernels(resources, "lss_plan_kernel"):
         assert private == 0, sym
+
+
+def test_bit_split_runs_three_workgroups_a_cu(resources):
+    """Its workgroups put two waves on each SIMD; six waves of at most 80 registers fit."""
+    for sym, vgprs, private in kernels(resources, "bit_split_kernel"):
+        assert vgprs <= 80 and private == 0, (sym, vgprs)
