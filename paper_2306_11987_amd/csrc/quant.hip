@@ -554,8 +554,14 @@ __global__ __launch_bounds__(kQThreads) void fwht_quant_kernel(QJob j0, QJob j1,
   int64_t k = 0, kp = 0;  // load and process positions
   int it = 0, ip = 0;
   int ss = 0;
-  Raw16<DT> raw[U], next[U];
-  auto load = [&](Raw16<DT>* raw, int64_t s0) {
+  // Each pass loads its own two steps.  With the next pass's loads beside them the 16-bit types
+  // held 91 registers and two workgroups a CU, without 77 and three (16384 x 4096 and 4096 x
+  // 4096 fp16: 49 and 44 to 46 us; 200 x 4096 and 11008 x 4096: 40.5 and 34.7).  The first loads
+  // go out before the maximum is formed for fp32 alone (16384 x 4096 and 4096 x 4096: 84 us, 88
+  // after it); fp16 takes 48.7 us so instead of 43.7.
+  constexpr bool EARLY = DT == kF32;
+  Raw16<DT> raw[U];
+  auto load = [&](int64_t s0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
@@ -564,12 +570,12 @@ __global__ __launch_bounds__(kQThreads) void fwht_quant_kernel(QJob j0, QJob j1,
       }
     }
   };
-  load(raw, 0);  // in flight while the maximum is formed
+  if constexpr (EARLY) load(0);
   const float a = reduce_parts(o.part, o.nparts);
   if (wg == 0 && threadIdx.x == 0) *o.amax_out = a;
   const float inv = a > 0.f ? 7.0f / a : 0.f;
   for (int64_t s0 = 0; s0 < g.steps; s0 += U) {
-    load(next, s0 + U);  // the next steps' loads, in flight while these are quantised
+    if (!EARLY || s0) load(s0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < g.steps) {
@@ -601,8 +607,6 @@ __global__ __launch_bounds__(kQThreads) void fwht_quant_kernel(QJob j0, QJob j1,
         }
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) raw[u] = next[u];
   }
 }
 

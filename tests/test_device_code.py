@@ -74,3 +74,11 @@ def test_bit_split_runs_three_workgroups_a_cu(resources):
     """Its workgroups put two waves on each SIMD; six waves of at most 80 registers fit."""
     for sym, vgprs, private in kernels(resources, "bit_split_kernel"):
         assert vgprs <= 80 and private == 0, (sym, vgprs)
+
+
+def test_quantiser_runs_three_workgroups_a_cu(resources):
+    """The 16-bit types; fp32 holds two (its raw data takes twice the registers)."""
+    for sym, vgprs, private in kernels(resources, "fwht_quant_kernel"):
+        assert private == 0, sym
+        if "ILi0E" not in sym:  # the first template argument: fp32
+            assert vgprs <= 80, (sym, vgprs)
