@@ -1135,32 +1135,39 @@ int resident_wgs(const void* f) {
   return n;
 }
 
-// Lanes per row (as a logarithm): a wave's steps are the rows it takes in turn times the
-// chunks a lane takes of each, for a grid of two workgroups per CU, and the group with the
-// fewest wins, a group wider than a wave counting one more per row for its barrier.  Ties go
-// to the largest power of two up to 64 that divides the row: no lane idles there, and it is
-// the choice wherever rows are many or their chunks a power of two.  Few rows, or 64-multiples
-// with odd factors, take wider groups (the last chunks of a row then leave lanes idle): 1003
-// rows of 832 and 1344 columns, fp32, with 4 lanes per row (8 workgroups) and with 64:
-// maximum 11.5 -> 3.6 us, bit split 28.4 -> 9.0 us, quantiser 16.1 -> 7.5 us.
-// Of several wider groups inside a wave with equal counts the widest is taken (14475 x 6016
-// fp32, maximum and quantiser: 187 -> 180 us, 189 with 8 lanes; 16384 x 7104: 227 -> 219).
-// The choice does not depend on the kernel, and grids of more than one round are multiples
-// of 8, so every kernel that walks a tensor reads a row on the same XCD and finds what fits
-// its L2 there (the quantiser of 16384 x 768 fp16 after a maximum pass that walked the
-// tensor in another order: 13.9 us, in this one 12.4 us).
+// Lanes per row (as a logarithm).  The default, the largest power of two up to 64 that divides
+// the row's chunks, leaves no lane idle; wider groups, up to the workgroup, take fewer steps a
+// row and idle in its last one.  Estimated time: the steps a wave takes of a row, and 0.4 of
+// one for its end (0.9 where a group spans waves and ends in a barrier), times the waves each
+// of the 1024 SIMDs runs one after the other or side by side, below three of which latency and
+// not throughput counts.  A wider group is taken where it saves a fifth by this estimate, and
+// inside a wave the widest of about equal ones, for its longer runs of memory.  Measured over
+// 8 to 512 lanes a row at 140 shapes:
+//   few rows, odd factors: 1003 x 832 and 1344 x 832 fp32 with 4 lanes and with 64: maximum 12.7
+//   and 6.0 us, quantiser 17.1 and 8.3; bit split of 300 x 2752 with 4 lanes 57 us, with 256 8.5;
+//   rows that fill the device: bit split of 81920 x 192 with 4 lanes 19.2 us, with 16 (a quarter
+//   of them idle) 25.4; of 8192 x 768 with 16 lanes 12.0, with 64 13.8; quantiser of 8192 x 768
+//   and 2112 x 768 10.9 and 12.7.
+// The choice does not depend on the kernel, and an unbatched grid of more than one round gives
+// each tensor a multiple of 8 workgroups (where it does not run out of rows), so every kernel
+// that walks a tensor reads a row on the same XCD and finds what fits its L2 there (the
+// quantiser of 16384 x 768 fp16 after a maximum pass that walked the tensor in another order:
+// 13.9 us, in this one 12.4 us).
 void choose_group(QJob& j) {
   if (j.rows <= 0) return;
-  constexpr int64_t cap = 512;
-  const int64_t chunks = j.cols / kVE;
-  auto steps = [&](int l) {
-    const int64_t rw = kQThreads >> l;
-    const int64_t rounds = (j.rows * j.batch + rw * cap - 1) / (rw * cap);
-    return rounds * (((chunks - 1) >> l) + 1 + (l > 6 ? 1 : 0));
+  const int64_t chunks = j.cols / kVE, rows = j.rows * j.batch;
+  auto cost = [&](int l) {
+    const int64_t steps = ((chunks - 1) >> l) + 1, threads = rows << l;
+    constexpr int64_t three = 3 * 1024 * 64;  // threads of three waves on each SIMD
+    return (double)(10 * steps + (l > 6 ? 9 : 4)) * (double)(threads > three ? threads : three);
   };
   int best = j.log2g;
-  for (int l = j.log2g + 1; (1 << l) <= kQThreads && (chunks >> (l - 1)) > 0; ++l)
-    if (steps(l) < steps(best) || (best != j.log2g && l <= 6 && steps(l) == steps(best))) best = l;
+  double c = 0.8 * cost(best);
+  for (int l = j.log2g + 1; (1 << l) <= kQThreads && (chunks >> (l - 1)) > 0; ++l) {
+    const double x = cost(l);
+    if (x < c || (best != j.log2g && l <= 6 && x <= 1.05 * c)) best = l;
+    if (x < c) c = x;
+  }
   j.log2g = best;
 }
 

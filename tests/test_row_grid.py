@@ -35,3 +35,25 @@ def test_one_tensor_takes_the_whole_grid():
         for r in (1, 100, 16384, 65536):
             (w, l), (w1, _) = H.debug_row_grid(r, 0, cols)
             assert w == min(needed(r, cols, l, False), 1024) and w1 == 0
+
+
+def default_group(cols):
+    """Largest power of two, of 4 to 64, that divides the row's 16-column chunks."""
+    l = 2
+    while l < 6 and (cols // 16) % (2 << l) == 0:
+        l += 1
+    return l
+
+
+@pytest.mark.parametrize("cols", [64, 192, 320, 448, 768, 832, 1088, 1344, 1536, 2304, 2944, 6016, 11008])
+def test_row_groups(cols):
+    """Rows that keep three waves on each of the 1024 SIMDs leave no lane idle (a wider group then
+    only adds work); a few rows spread over enough lanes to finish in a few steps."""
+    d, chunks = default_group(cols), cols // 16
+    for batch in (1, 160):
+        for rows in (3 * 1024 * 64 >> d, 100000, 300000):
+            rows = -(-max(rows, 3 * 1024 * 64 >> d) // batch)
+            assert H.debug_row_grid(rows, 0, cols, batch=batch)[0][1] == d, (rows, batch)
+    for rows in (1, 64, 300):
+        l = H.debug_row_grid(rows, 0, cols)[0][1]
+        assert l >= d and (chunks - 1 >> l) + 1 <= 3, (rows, l)
