@@ -202,17 +202,25 @@ int grad_bn(int64_t M, int64_t N, int splits) {
 }
 
 // Tile width of a forward (INT4 x INT4) GEMM by the same rule, the tiles of all batches
-// counted; its 128-wide tiles use 64 x 64 wave tiles.  They also take products of up to 16
-// stages whose 256-wide tiles would leave half of a second round empty (kernel times, 256 and
-// 128 wide: 640 tiles, 10240 x 1024 -> 2048, 28.4 and 23.9 us, 768, 8192 x 1024 -> 3072, 28.9
-// and 27.0; longer products and further rounds lose: 688 tiles, 11000 x 8192 -> 2048, 151 and
-// 162 us, 1280, 10240 x 2048 -> 4096, 73.6 and 79.4 us).
+// counted; its 128-wide tiles use 64 x 64 wave tiles.  They also take products whose 256-wide
+// tiles would leave most of a second round of 512 empty, while the product is short: kernel
+// times of 128- over 256-wide tiles, K = 128 to 2048 (1 to 16 stages), fp16 and fp32 outputs:
+//   520 to 640 tiles      0.82 to 0.96 and 0.84 to 0.98 at every K;
+//   688 to 768 tiles      0.88 to 0.97 up to 8 stages, 0.97 to 1.05 from 10 on, fp32 0.99 to
+//                         1.10 (its epilogue moves twice the bytes), batched, one or two
+//                         stages, 0.84 to 0.95 and 0.91 to 1.00;
+//   896 tiles and more, or longer products: no gain (688 tiles, 64 stages, 151 and 162 us;
+//                         1280 tiles, 16 stages, 73.6 and 79.4).
+template <int DT>
 int fwd_bn(int64_t M, int64_t N, int64_t K, int splits, int64_t batch) {
   if (splits > 1) return kBN;
   if (g_bn_override) return g_bn_override;
   const int64_t bm = tile_m<true>();
   const int64_t t256 = ((M + bm - 1) / bm) * ((N + kBN - 1) / kBN) * (batch > 0 ? batch : 1);
-  return 4 * t256 <= 3 * 512 || (t256 > 512 && t256 <= 768 && K <= 16 * kKS) ? kMidBN : kBN;
+  if (4 * t256 <= 3 * 512) return kMidBN;
+  if (t256 > 512 && t256 <= 640 && K <= 16 * kKS) return kMidBN;
+  if (t256 > 640 && t256 <= 768 && K <= 8 * kKS && (DT != kF32 || batch > 0)) return kMidBN;
+  return kBN;
 }
 
 // the Hadamard block is a template parameter of the gradient epilogues
@@ -257,7 +265,7 @@ hipError_t gemm_b(hipStream_t s, const GemmArgs& g, int splits, int id) {
     }
     return hipErrorInvalidValue;
   } else {
-    if (fwd_bn(g.M, g.N, g.K, splits, g.batch) == kMidBN) return gemm_t<BM, A4, EPI, DT, 0, kMidBN, false, 0, TRA>(s, g, splits, id);
+    if (fwd_bn<DT>(g.M, g.N, g.K, splits, g.batch) == kMidBN) return gemm_t<BM, A4, EPI, DT, 0, kMidBN, false, 0, TRA>(s, g, splits, id);
     return gemm_t<BM, A4, EPI, DT, 0, kBN, false, 0, TRA>(s, g, splits, id);
   }
 }
