@@ -98,7 +98,7 @@ size_t dx_gemm_partial(int64_t N, int64_t D, int64_t C) {
   return al(gemm_partial_bytes(N, D, gemm_splits(N, D, C, false, true)));
 }
 size_t dw_gemm_partial(int64_t N, int64_t D, int64_t C) {
-  return al(gemm_partial_bytes(C, D, gemm_splits(C, D, (N + 127) / 128 * 128, false, true)));
+  return al(gemm_partial_bytes(C, D, gemm_splits(C, D, (N + 127) / 128 * 128, false, true, true)));
 }
 // The forward product of hq_linear_fwd runs on the FP6 MFMA (the quantizer then also writes
 // the codes as FP6 into the workspace) when the product is large enough for the faster
@@ -174,7 +174,7 @@ int64_t lsq_parts_dx(int64_t N, int64_t D, int64_t C, int k = -1) {
   return gemm_epi_parts(N, D, gemm_splits(N, D, C, false, true), 0, k);
 }
 int64_t lsq_parts_dw(int64_t N, int64_t D, int64_t C, int k = -1) {
-  return gemm_epi_parts(C, D, gemm_splits(C, D, rup(N, kPad), false, true), 0, k);
+  return gemm_epi_parts(C, D, gemm_splits(C, D, rup(N, kPad), false, true, true), 0, k);
 }
 size_t lsq_parts_bytes(int64_t N, int64_t D, int64_t C, bool dx, bool dw) {
   return (dx ? al(8 * lsq_parts_dx(N, D, C)) : 0) + (dw ? al(8 * lsq_parts_dw(N, D, C)) : 0);
@@ -531,7 +531,7 @@ hqlss_status do_grads(const lss_plan_t* p, const hqlss_saved_t* sv, void* dX, vo
   if (want_dx) part_dx = w.take<int32_t>(gemm_partial_bytes(N, D, sp_dx));
   uint8_t* XtT = nullptr;
   int32_t* part_dw = nullptr;
-  const int sp_dw = gemm_splits(C, D, Kp, false, true);
+  const int sp_dw = gemm_splits(C, D, Kp, false, true, true);
   if (want_dw) {
     XtT = w.take<uint8_t>(D * Kp / 2);
     part_dw = w.take<int32_t>(gemm_partial_bytes(C, D, sp_dw));

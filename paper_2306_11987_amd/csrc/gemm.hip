@@ -339,7 +339,7 @@ void gemm_set_split_override(int splits) { g_split_override = splits < 0 ? 0 : s
 int gemm_split_override() { return g_split_override; }
 void gemm_set_tile_override(int bn) { g_bn_override = (bn == kMidBN || bn == kBN) ? bn : 0; }
 
-int gemm_splits(int64_t M, int64_t N, int64_t K, bool a_int4, bool b_int4) {
+int gemm_splits(int64_t M, int64_t N, int64_t K, bool a_int4, bool b_int4, bool a_kmajor) {
   (void)b_int4;
   if (g_split_override) return g_split_override;
   const int64_t bm = a_int4 ? tile_m<true>() : tile_m<false>();
@@ -348,11 +348,16 @@ int gemm_splits(int64_t M, int64_t N, int64_t K, bool a_int4, bool b_int4) {
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int64_t stages = (K + kKS - 1) / kKS;
   if (2 * tiles >= slots || stages < 16) return 1;
-  // A split costs its partials and the reduction, 5 us and more: with an eighth of the CUs
-  // holding a 128 x 128 tile it is of use from about 24 stages (kernel times, split and not:
-  // 2048^3, 16 stages, forward 21.1 and 12.0 us; N = 2048, 1024 -> 2048, 16 stages, dX 13.7
-  // and 11.6; N = 1024, 1024 -> 4096, 32 stages, dX 13.5 and 15.6).
-  if (stages < 24 && ((M + 127) / 128) * ((N + 127) / 128) >= 32) return 1;
+  // A split costs its partials and the reduction: up to 23 stages (then two splits) it pays only
+  // where it evens out a bad number of tiles.  Whole calls, not split minus split, 32 to 168
+  // tiles of 128 x 128, fp16 and fp32, b = 32 and 128, at 16 and at 23 stages: forward always
+  // less (2048^3 21.1 and 12.0 us); gradients up to 64 tiles (64-row tiles) -4 and -2 us, b = 128
+  // (64 x 128 of them) -2 and +1; dX with 72 to 80 tiles -2 and +2, from 96 on -4 and -1; dW,
+  // whose loop takes longer a stage, with 72 to 110 tiles -3 and +2, from 128 on -4 and -1.  The
+  // bad ones turn at 18 to 20 stages.
+  const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
+  const bool uneven = !a_int4 && t128 > 64 && t128 < (a_kmajor ? 112 : 90);
+  if (t128 >= 32 && stages < (uneven ? 20 : 24)) return 1;
   int64_t s = slots / tiles;        // all splits resident at once (no second round)
   const int64_t smax = stages / 8;  // keep >= 8 stages per split
   if (s > smax) s = smax;

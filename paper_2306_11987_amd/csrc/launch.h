@@ -161,7 +161,8 @@ struct GemmArgs {
 };
 // Split-K factor the launcher uses for this shape (1 = no split), and the int32 partial
 // buffer it then needs (splits x M x N words).  A non-zero override forces the factor.
-int gemm_splits(int64_t M, int64_t N, int64_t K, bool a_int4, bool b_int4);
+// a_kmajor as in GemmArgs.
+int gemm_splits(int64_t M, int64_t N, int64_t K, bool a_int4, bool b_int4, bool a_kmajor = false);
 size_t gemm_partial_bytes(int64_t M, int64_t N, int splits);
 void gemm_set_split_override(int splits);
 void gemm_set_tile_override(int bn);
