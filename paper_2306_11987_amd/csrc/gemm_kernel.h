@@ -208,21 +208,26 @@ __device__ __forceinline__ bool tile_of(int T, int tiles_n, int& tm, int& tn) {
 
 // 16-byte LDS-DMA load (global_load_lds_dwordx4): each lane's 16 bytes at base + off land at
 // lds_base + 16 * lane.  The base is the tile's and stage's (scalar), the offset the lane's
-// within the tile (below 2^31: at most 128 or 256 rows of up to 2^24 bytes), so that a load
-// takes no vector arithmetic.  Issued as inline assembly with a memory clobber: the compiler
+// within the tile (unsigned, below 2^27: at most 256 rows of less than 2^19 bytes, which the
+// accumulators' limits see to), so that a load takes no vector arithmetic.  Issued as inline
+// assembly with a memory clobber: the compiler
 // keeps it in program order with every other memory access, but does not treat it as a
 // pending LDS write; it would otherwise wait for every such load before any later LDS
 // read, including the loads just issued for a later stage.  The stage pipeline waits for
-// exactly the loads each stage needs.
+// exactly the loads each stage needs.  An LDS-DMA load needs one wait state after a scalar
+// write of M0, its LDS address; the compiler adds it for its own loads, not around assembly.
+// (It costs the int8 loops nothing; the FP6 gradient loops 1 and 3 %, and more in the ways
+// tried around it: the lane's address added in its place, or one M0 for a run of loads with
+// their places as instruction offsets.)
 __device__ __forceinline__ void dma16(const uint8_t* base, uint32_t off, void* lds_base) {
   const uint32_t l = (uint32_t)(uintptr_t)(lds_void*)lds_base;
-  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(l) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(l) : "memory");
 }
 
 // The same from a lane's own address.
 __device__ __forceinline__ void dma16_at(const void* p, void* lds_base) {
   const uint32_t l = (uint32_t)(uintptr_t)(lds_void*)lds_base;
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(p), "{m0}"(l) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "{m0}"(l) : "memory");
 }
 
 // s_waitcnt: vector-memory count <= n, LDS count 0 (gfx9 encoding: vmcnt [3:0] and

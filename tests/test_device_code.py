@@ -82,3 +82,44 @@ def test_quantiser_runs_three_workgroups_a_cu(resources):
         assert private == 0, sym
         if "ILi0E" not in sym:  # the first template argument: fp32
             assert vgprs <= 80, (sym, vgprs)
+
+
+def instructions(obj):
+    for line in subprocess.Popen([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", "--no-leading-addr",
+                                  obj], stdout=subprocess.PIPE, text=True).stdout:
+        line = line.split("//")[0].strip()
+        if line and not line.endswith(":"):
+            yield line
+
+
+def registers(operand):
+    """Scalar register numbers of s5 or s[4:5]."""
+    if operand.startswith("s["):
+        lo, _, hi = operand[2:-1].partition(":")
+        return set(range(int(lo), int(hi or lo) + 1))
+    return {int(operand[1:])} if operand[1:].isdigit() and operand[0] == "s" else set()
+
+
+def test_lds_dma_loads_wait_for_their_scalars(objects):
+    """The loads are inline assembly, around which the compiler adds no wait states: one between a
+    scalar write of M0 (the LDS address) and the load, five between a vector instruction's write of
+    a scalar register and a load that reads it as its address."""
+    loads = 0
+    for obj in objects:
+        last = []  # (instruction, wait states it gives by itself)
+        for ins in instructions(obj):
+            op, _, rest = ins.partition(" ")
+            args = [a.strip() for a in rest.split(",")]
+            if op.startswith("global_load_lds"):
+                loads += 1
+                reads = set().union(*(registers(a) for a in args))
+                states = 0
+                for p_op, p_args, given in reversed(last):
+                    if p_op.startswith("s_") and p_args[0] == "m0":
+                        assert states >= 1, f"{p_op} {p_args} directly before {ins}"
+                    if p_op.startswith("v_") and reads & registers(p_args[0]):
+                        assert states >= 5, f"{p_op} {p_args} before {ins}"
+                    states += given
+            given = 1 + int(args[0], 0) if op == "s_nop" else 1
+            last = (last + [(op, args, given)])[-6:]
+    assert loads > 10000
