@@ -380,8 +380,7 @@ size_t gemm_partial_bytes(int64_t M, int64_t N, int splits) {
 hipError_t launch_gemm(hipStream_t s, int epi, int dt, bool a_int4, bool b_int4, const GemmArgs& g,
                        int splits, int32_t* partial) {
   if (!b_int4) return hipErrorInvalidValue;
-  if (epi != kEpiAcc && (a_int4 || (epi != kEpiDw && epi != kEpiDwL) || g.a_kmajor) &&
-      gemm_small(g.M, g.N, splits, g.batch))
+  if ((a_int4 || (epi != kEpiDw && epi != kEpiDwL) || g.a_kmajor) && gemm_small(g.M, g.N, splits, g.batch))
     return launch_gemm_small(s, epi, dt, a_int4, g);
   if (a_int4) {
     if (epi == kEpiFwd) return run_dt<true, kEpiFwd>(s, dt, g, splits, partial, kKGemmFwd);

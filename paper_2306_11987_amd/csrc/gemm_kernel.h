@@ -1,7 +1,8 @@
 // Device side of the integer and FP6 GEMMs of HQ-MM / LSS-MM (internal to libhqlss):
 // operand layouts, the tile order, the kernel template with its main loops and fused
 // epilogues, and its launcher.  Included by the translation units that instantiate it
-// (gemm.hip: int8 MFMA route; gemm6.hip: FP6 MFMA route); see gemm.hip for the design.
+// (gemm.hip: int8 MFMA route; gemm_small.hip: its 64-row tiles; gemm6.hip: FP6 MFMA route); see
+// gemm.hip for the design.
 #pragma once
 #include "common.h"
 #include "launch.h"
@@ -64,7 +65,7 @@ struct Cfg {
   static constexpr int DMA = A_BPW + B_BPW;  // 1 KB LDS-DMA loads per wave per stage
   static constexpr int OCC = BM == 128 ? 2 : 1;  // workgroups per CU (at least)
   // 64-row tiles run where a CU holds a workgroup or two: with nothing else to hide a load
-  // behind, four or five stages of loads stay in flight
+  // behind, NBUF - 1 = five stages of loads stay in flight, or three where a stage takes more LDS
   static constexpr int NBUF = BM == kSmallBM ? (STAGE <= 12 * 1024 ? 6 : 4)
                               : (F6 && BM == 256) ? HQLSS_F6_NBUF256 : (OCC == 2 && !A4) ? 2 : 3;
   static constexpr int LDS_MAIN = NBUF * STAGE;
@@ -142,6 +143,18 @@ __device__ __forceinline__ void fwht_lane(int* v, int lane) {
   }
 }
 
+// a / b for a >= 0, b > 0 (uniform): a quotient below 2^22 from the reciprocal is off by at
+// most one, corrected by its remainder; it takes a third of the instructions of the integer
+// division, and a workgroup divides five times before its first load.
+__device__ __forceinline__ int quick_div(int a, int b) {
+  if (a >= (1 << 22)) return a / b;
+  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+  const int r = a - q * b;
+  q += r >= b ? 1 : 0;
+  q -= r < 0 ? 1 : 0;
+  return __builtin_amdgcn_readfirstlane(q);
+}
+
 // XCD-aware tile order.  The hardware dispatches workgroups to the 8 XCDs round-robin by
 // linear id, so workgroup b runs on XCD b % 8.  The T tiles (row-major, n fastest) are cut
 // into 8 contiguous chunks, one per XCD, and the j-th workgroup of XCD x takes the j-th
@@ -158,18 +171,6 @@ __device__ __forceinline__ void fwht_lane(int* v, int lane) {
 // G operand panels of one side and 64 / G of the other in that XCD's L2, instead of the
 // two rows by all columns of the plain order.  The chunk's partial first and last rows
 // come after its whole rows, in the plain order.
-// a / b for a >= 0, b > 0 (uniform): a quotient below 2^22 from the reciprocal is off by at
-// most one, corrected by its remainder; it takes a third of the instructions of the integer
-// division, and a workgroup divides five times before its first load.
-__device__ __forceinline__ int quick_div(int a, int b) {
-  if (a >= (1 << 22)) return a / b;
-  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
-  const int r = a - q * b;
-  q += r >= b ? 1 : 0;
-  q -= r < 0 ? 1 : 0;
-  return __builtin_amdgcn_readfirstlane(q);
-}
-
 template <int G>
 __device__ __forceinline__ int grouped_tile(int j, int s, int len, int tiles_n) {
   const int rf = quick_div(s + tiles_n - 1, tiles_n), rl = quick_div(s + len, tiles_n);

@@ -4,7 +4,8 @@
 // Such a product is bound by latency: a CU holds one workgroup, which waits for every stage
 // of its operands.  Tiles of 64 x 64 (64 x 128 for Hadamard blocks of 128, which a wave's
 // tile must hold) give up to four times as many workgroups of two waves, and six stage
-// buffers (48 to 72 KB of LDS) keep five stages of loads in flight instead of one or two
+// buffers (four for 64 x 128 int8 tiles; 48 to 72 KB of LDS) keep five stages of loads (three)
+// in flight instead of one or two
 // (16 x 1024 -> 4096, b = 128, eight stages: 8.1 -> 5.9 us; 128 x 256 -> 256: forward 5.1 ->
 // 4.5, dX 6.0 -> 5.4, dW 5.2 -> 4.5 us).
 // Kernel, epilogues and results are those of gemm_kernel.h.
@@ -16,7 +17,7 @@ namespace {
 
 template <bool A4, int EPI, int DT, bool TRA>
 hipError_t small_b(hipStream_t s, const GemmArgs& g, int id) {
-  if constexpr (EPI == kEpiFwd) {
+  if constexpr (EPI == kEpiFwd || EPI == kEpiAcc) {
     return gemm_t<kSmallBM, A4, EPI, DT, 0, kNarrowBN, false, 0, TRA>(s, g, 1, id);
   } else {
     switch (g.log2b) {
@@ -48,8 +49,14 @@ hipError_t small_dt(hipStream_t s, int dt, const GemmArgs& g, int id) {
 int gemm_small_bn(int log2b) { return log2b == 7 ? kMidBN : kNarrowBN; }
 
 hipError_t launch_gemm_small(hipStream_t s, int epi, int dt, bool a_int4, const GemmArgs& g) {
-  if (a_int4) return epi == kEpiFwd ? small_dt<true, kEpiFwd>(s, dt, g, kKGemmFwd) : hipErrorInvalidValue;
+  if (a_int4) {
+    if (epi == kEpiFwd) return small_dt<true, kEpiFwd>(s, dt, g, kKGemmFwd);
+    return epi == kEpiAcc ? small_b<true, kEpiAcc, kF32, false>(s, g, kKGemmAcc) : hipErrorInvalidValue;
+  }
   switch (epi) {
+    case kEpiAcc:
+      return g.a_kmajor ? small_b<false, kEpiAcc, kF32, true>(s, g, kKGemmAcc)
+                        : small_b<false, kEpiAcc, kF32, false>(s, g, kKGemmAcc);
     case kEpiDx: return small_dt<false, kEpiDx>(s, dt, g, kKGemmDx);
     case kEpiDxL: return small_dt<false, kEpiDxL>(s, dt, g, kKGemmDx);
     case kEpiDw: return small_dt<false, kEpiDw, true>(s, dt, g, kKGemmDw);
