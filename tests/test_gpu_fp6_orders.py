@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kind,budget_div", [("lognormal", 1), ("sparse_rows", 4)])
 @pytest.mark.parametrize("N,D,C", [(1, 64, 64), (15, 128, 64), (1023, 64, 192), (1024, 192, 64), (1025, 64, 64),
-                                   (2063, 320, 128), (16385, 64, 64)])
+                                   (2063, 320, 128), (16385, 64, 64), (49153, 64, 64), (65536, 64, 64)])
 def test_fp6_orders(N, D, C, kind, budget_div):
     H = need_gpu()
     k, dt, budget = 4, "bf16", max(1, N // budget_div)
