@@ -58,7 +58,9 @@ hqlss_status check_bwd_overflow(int64_t N, int64_t D, int64_t C, int log2_block)
   if (f * kmax >= kI32) return HQLSS_ERR_OVERFLOW;
   const long double sc = 196.0L * 49.0L * (long double)C * 49.0L * (long double)D * 65536.0L;
   if (sc >= 18446744073709551615.0L) return HQLSS_ERR_OVERFLOW;
-  if (N > 65536) return HQLSS_ERR_SHAPE;  // one-workgroup sampler keeps <= 64 tokens per thread
+  // the sampler's quotient (plan.hip) takes R <= 2 N < 2^18 and S <= 2 N 2^32 < 2^50, and the FP6
+  // orders count up to 64 tokens a thread in halves of a word
+  if (N > 65536) return HQLSS_ERR_SHAPE;
   return HQLSS_OK;
 }
 
