@@ -129,8 +129,8 @@ __device__ __forceinline__ void load8u(const uint32_t* p, int t0, int n8, uint32
 //   - R c >= S and R c 2^e <= S are comparisons of c with quotients formed once;
 //   - the kept list is compacted in LDS and leaves in whole lines (8 scattered words a thread
 //     before).
-// N = 128 (five rounds): 11.3 -> 9.4 us; N = 16384, lognormal rows, budget N (no round):
-// 10.2 -> 7.5 us, Pareto rows (eight rounds): 37.9 -> 25.6 us.
+// N = 128 (five rounds): 11.3 -> 8.6 us; N = 16384, lognormal rows, budget N (no round), event
+// times: 11.5 -> 9.0 us; Pareto rows (eight rounds): 37.9 -> 23.7 us.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void lss_plan_kernel(
     const int32_t* __restrict__ sumsq_up, const uint32_t* __restrict__ scores, int64_t pitch,
