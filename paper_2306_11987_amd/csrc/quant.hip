@@ -1224,7 +1224,7 @@ void fit_grid(QJob& a, QJob& b, int cap, bool flat = false) {
     if (wb < 8) wb = 8;
     if (wb > nb) wb = nb;
   }
-  int64_t wa = cap - wb;
+  int64_t wa = (cap - wb) / 8 * 8;
   if (wa > na) wa = na;
   a.wg = (int)wa;
   b.wg = (int)wb;

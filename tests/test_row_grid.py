@@ -28,6 +28,8 @@ def test_no_job_loses_its_share_of_the_grid(cap, flat):
                     share = cap * r // (r0 + r1)
                     want = min(needed(r, cols, l, flat), max(1, 7 * share // 8 // 8 * 8))
                     assert w >= want, (cols, r0, r1, wg, want)
+                    # rows taken in several rounds stay on one XCD from kernel to kernel
+                    assert w == needed(r, cols, l, flat) or w % 8 == 0, (cols, r0, r1, wg)
 
 
 def test_one_tensor_takes_the_whole_grid():
