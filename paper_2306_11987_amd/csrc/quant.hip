@@ -278,14 +278,18 @@ struct Geo {
   }
 };
 
-// The row groups of Geo with 32 elements a lane and half the lanes a row: the second half of
-// the workgroup's threads takes the rows of the next round, so that a row stays on the
-// workgroup (and XCD) that Geo gives it.
+// The row groups of Geo with 32 elements a lane: half the steps a row where Geo takes an even
+// number of whole ones, else half the lanes.  The second half of the workgroup's threads then
+// takes the rows of the next round, so that a row stays on the workgroup (and XCD) that Geo
+// gives it.  (Half the lanes throughout left half of the threads idle wherever there is no next
+// round: 8192 x 4096 beside a small weight, fp16, b = 32: 19.1 us, 16.4 with 16 elements a lane.)
 struct Geo32 {
   int lane, sub, G, iters, chunks, spare;
   int64_t first_row, row_step, rows, steps;
   __device__ Geo32(const QJob& j, int wg) {
-    const int l = j.log2g - 1;  // lanes per row; log2g >= 2, and >= 3 where a block has 128 columns
+    const int64_t c16 = j.cols / kVE;
+    const bool whole = c16 % (int64_t(2) << j.log2g) == 0;
+    const int l = whole ? j.log2g : j.log2g - 1;  // lanes per row; log2g >= 2, and >= 3 where a block has 128 columns
     lane = threadIdx.x & 63;
     G = 1 << l;
     sub = threadIdx.x & (G - 1);
@@ -296,7 +300,7 @@ struct Geo32 {
     const int64_t round = (int64_t)j.wg * rw;
     auto row = [&](int t) { return (int64_t)wg * rw + (t >> l) % rw + (t >> l) / rw * round; };
     first_row = row(threadIdx.x);
-    row_step = 2 * round;
+    row_step = whole ? round : 2 * round;
     rows = j.rows;
     const int64_t row0 = row(threadIdx.x & ~63u);  // the wave's first
     steps = row0 < rows ? (rows - row0 + row_step - 1) / row_step * iters : 0;
@@ -383,8 +387,8 @@ __global__ __launch_bounds__(kQThreads) void fwht_absmax_kernel(QJob j0, QJob j1
   constexpr int U = 2;
   // blocks of 32 columns and more: the two steps are one of 32 elements in a row, one lane
   // exchange less an element (at b = 128 the one that goes through LDS); vector instructions
-  // bound this pass there (16384 x 4096 and 4096 x 4096 bf16, b = 128: 42.5 -> 40.3 us;
-  // 16384 x 768 and 3072 x 768 fp16, b = 32: 8.4 -> 7.6).  Not for fp32, whose lanes would
+  // bound this pass there (event times, 16384 x 4096 and 4096 x 4096 fp16, b = 128: 40.9 -> 37.2
+  // us; 16384 x 768 and 3072 x 768, b = 32: 10.1 -> 9.0).  Not for fp32, whose lanes would
   // load 128 bytes each (1003 x 832: 4.6 -> 5.2)
   constexpr bool WIDE = LOG2B >= 5 && DT != kF32;
   __shared__ float red[kQWaves];

@@ -7,9 +7,11 @@ for bit, outputs as in the other parity tests.
 """
 import numpy as np
 import pytest
+import torch
 
 import oracle as O
-from gpu_util import check_backward_acc, check_float_output, check_forward, check_plan, need_gpu, run_backward, run_forward, say
+from gpu_util import (check_backward_acc, check_float_output, check_forward, check_plan, need_gpu, run_backward, run_forward,
+                      say, TORCH_DT)
 from test_gpu_lsq import _case, _steps, check_forward_codes, run_forward_lsq
 from test_gpu_variants import _check_choice
 
@@ -74,3 +76,27 @@ def test_sampler_sizes(N, budget):
     b = O.lss_backward(G, f, budget, 4, 1)
     _, plan, _, _ = run_backward(H, G, saved, N, 64, 64, 2, "f16", budget, 4, 1)
     check_plan(plan, b)
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("N,D,C,k", [(9, 2048, 64, 5), (8200, 2048, 64, 7), (16400, 1024, 64, 5), (16385, 768, 3072, 5),
+                                     (700, 4096, 11008, 7), (4099, 1088, 8192, 6), (130, 11008, 64, 5)])
+def test_maximum_sees_every_place(N, D, C, k, dt):
+    """One value in a tensor of zeros is its own maximum wherever it sits: the first and last rows,
+    columns and lanes, rows of the second round, either tensor."""
+    H = need_gpu()
+    say(f"maximum {N}x{D} {C}x{D} k={k} {dt}")
+    X, W = (torch.zeros(r, D, device="cuda", dtype=TORCH_DT[dt]) for r in (N, C))
+    saved = H.Saved.empty(N, D, C)
+    ws = H.workspace(H.WS_FWD, N, D, C)
+    Y = torch.empty(N, C, device="cuda", dtype=TORCH_DT[dt])
+    rng = np.random.default_rng(N + D)
+    for i, T in enumerate((X, W)):
+        rows = T.shape[0]
+        at = {(0, 0), (rows - 1, D - 1), (rows - 1, 0), (0, D - 1), (rows // 2, D // 2 + 31)}
+        at |= {(min(rows - 1, q), int(rng.integers(D))) for q in (7, 8, 511, 4095, 8127, 8128, 8191, 8192)}
+        for n, (r, c) in enumerate(sorted(at)):
+            T[r, c] = 1.0 + n
+            H.hq_linear_fwd(X, W, Y, saved, k, ws)
+            assert saved.amax.cpu()[i].item() == 1.0 + n, (i, r, c)
+            T[r, c] = 0.0
